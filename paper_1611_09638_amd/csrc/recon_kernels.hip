@@ -643,95 +643,6 @@ hipError_t launch_prolong_add(T *u, const T *e, int n, hipStream_t s)
     return hipGetLastError();
 }
 
-// Coarsest level in one workgroup, LDS resident: b made mean-free, u = 0,
-// then the palindromic red/black sequence (pairs of red, black, then a final
-// red), then the mean of u removed.  n^3 <= 4096.
-template <typename T>
-__global__ void __launch_bounds__(1024) k_coarse_solve(T *__restrict__ ug, const T *__restrict__ ag,
-                                                       const T *__restrict__ bg, int n, T inv_scale, T a_min,
-                                                       int pairs)
-{
-    __shared__ T u[4096], a[4096], b[4096];
-    __shared__ double red[1024];
-    const int n3 = n * n * n, t = threadIdx.x;
-    double sb = 0.0;
-    for (int p = t; p < n3; p += blockDim.x) {
-        a[p] = ag[p];
-        b[p] = bg[p];
-        u[p] = 0;
-        sb += (double)bg[p];
-    }
-    red[t] = sb;
-    __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
-    }
-    const T mb = (T)(red[0] / n3);
-    __syncthreads();
-    for (int p = t; p < n3; p += blockDim.x) b[p] -= mb;
-    __syncthreads();
-    // Each thread keeps its nodes' neighbour offsets, face coefficients, their
-    // sum and b in registers: only u changes between passes.  The arithmetic
-    // per relaxation is unchanged (faces in the order +i, -i, +j, -j, +k, -k).
-    constexpr int NPT = 4096 / 1024;
-    int q[NPT][6], col[NPT];
-    T cf[NPT][6], den[NPT], bv[NPT];
-#pragma unroll
-    for (int r = 0; r < NPT; ++r) {
-        const int p = t + r * 1024;
-        const int pp = p < n3 ? p : 0;
-        const int i = pp / (n * n), j = (pp / n) % n, k = pp % n;
-        col[r] = p < n3 ? ((i + j + k) & 1) : -1;
-        q[r][0] = (wrapc(i + 1, n) * n + j) * n + k;
-        q[r][1] = (wrapc(i - 1, n) * n + j) * n + k;
-        q[r][2] = (i * n + wrapc(j + 1, n)) * n + k;
-        q[r][3] = (i * n + wrapc(j - 1, n)) * n + k;
-        q[r][4] = (i * n + j) * n + wrapc(k + 1, n);
-        q[r][5] = (i * n + j) * n + wrapc(k - 1, n);
-        const T an = a[pp];
-        T d = 0;
-#pragma unroll
-        for (int f = 0; f < 6; ++f) {
-            cf[r][f] = facec(an, a[q[r][f]], a_min);
-            d += cf[r][f];
-        }
-        den[r] = d;
-        bv[r] = b[pp];
-    }
-    const int passes = 2 * pairs + 1;
-    for (int ps = 0; ps < passes; ++ps) {
-        const int colour = ps & 1;
-#pragma unroll
-        for (int r = 0; r < NPT; ++r) {
-            if (col[r] != colour) continue;
-            T num = 0;
-#pragma unroll
-            for (int f = 0; f < 6; ++f) num += cf[r][f] * u[q[r][f]];
-            u[t + r * 1024] = (num - bv[r] * inv_scale) / den[r];
-        }
-        __syncthreads();
-    }
-    double su = 0.0;
-    for (int p = t; p < n3; p += blockDim.x) su += (double)u[p];
-    red[t] = su;
-    __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
-    }
-    const T mu = (T)(red[0] / n3);
-    for (int p = t; p < n3; p += blockDim.x) ug[p] = u[p] - mu;
-}
-
-template <typename T>
-hipError_t launch_coarse_solve(T *u, const T *a, const T *b, int n, T scale, T a_min, int pairs, hipStream_t s)
-{
-    if (n * n * n > 4096) return hipErrorInvalidValue;
-    k_coarse_solve<T><<<1, 1024, 0, s>>>(u, a, b, n, (T)1 / scale, a_min, pairs);
-    return hipGetLastError();
-}
-
 __global__ void k_cast_f32(const double *__restrict__ s, float *__restrict__ d, long n3)
 {
     for (long p = blockIdx.x * 256L + threadIdx.x; p < n3; p += 256L * gridDim.x) d[p] = (float)s[p];
@@ -987,7 +898,6 @@ hipError_t launch_add_correction(double *u, const Z *z, long n3, hipStream_t s)
     template hipError_t launch_residual<T>(const T *, const T *, const T *, T *, int, T, T, hipStream_t);          \
     template hipError_t launch_restrict<T>(const T *, T *, int, hipStream_t);                                      \
     template hipError_t launch_prolong_add<T>(T *, const T *, int, hipStream_t);                                   \
-    template hipError_t launch_coarse_solve<T>(T *, const T *, const T *, int, T, T, int, hipStream_t);            \
     template hipError_t launch_dots_zr_zq<T>(const T *, const double *, const double *, long, Part &, hipStream_t); \
     template hipError_t launch_update_pq<T>(const T *, const double *, double *, double *, double, int, double,     \
                                             bool, const double *, Part &, hipStream_t);                           \

@@ -1,0 +1,51 @@
+"""The small levels of the V-cycle (one workgroup from 16^3 down) against the
+FP64 oracle, on every chain of edges that it has an instance for and on
+hierarchies that enter it from a larger level."""
+import numpy as np
+import pytest
+
+import oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+# (edge, coarsest edge, pre-sweeps, post-sweeps)
+CYCLES = [(2, 2, 2, 2), (4, 4, 2, 2), (4, 2, 2, 2), (6, 6, 2, 2), (8, 8, 2, 2), (8, 4, 2, 2), (8, 2, 2, 2),
+          (10, 10, 2, 2), (12, 12, 2, 2), (12, 6, 2, 2), (14, 14, 2, 2), (16, 16, 2, 2), (16, 8, 2, 2),
+          (16, 4, 2, 2), (16, 2, 2, 2), (16, 8, 1, 3), (16, 8, 0, 1), (16, 8, 2, 0), (20, 10, 2, 2), (24, 6, 2, 2),
+          (24, 12, 2, 2), (28, 14, 2, 2), (32, 16, 2, 2), (32, 4, 1, 1), (40, 10, 2, 2), (128, 8, 2, 2)]
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def rel(a, b):
+    return np.linalg.norm(a - b) / np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("pairs", [64, 3, 0])
+@pytest.mark.parametrize("n,cn,pre,post", CYCLES)
+def test_small_cycle_against_oracle(torch_cuda, n, cn, pre, post, pairs):
+    """FP64 to 1e-12 (the oracle's own rounding over the cycle); FP32 to 1e-4:
+    the cycle applies about 130 relaxations, each with a relative rounding of
+    a few 6e-8, to a field whose smooth part the coarsest level has scaled up
+    by less than 100."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    if pairs != 64 and n > 40:
+        pytest.skip("the count of coarsest sweeps is covered by the smaller grids")
+    rng = np.random.default_rng(500 + n + cn)
+    a = np.exp(1.5 * rng.normal(size=(n, n, n)))
+    r = rng.normal(size=(n, n, n))
+    r -= r.mean()
+    kw = dict(coarse_n=cn, n_pre=pre, n_post=post, coarse_sweeps=pairs)
+    z = orc.vcycle(a, r, orc.Config(**kw))
+    rec = binding.Recon(n, binding.Config(precision=binding.MIXED, **kw))
+    g = rec.vcycle(torch.from_numpy(a).cuda(), torch.from_numpy(r).cuda()).cpu().numpy()
+    assert rel(g, z) < 1e-12
+    g = rec.vcycle(torch.from_numpy(a).float().cuda(), torch.from_numpy(r).float().cuda()).double().cpu().numpy()
+    assert rel(g, z) < 1e-4

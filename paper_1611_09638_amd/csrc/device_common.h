@@ -257,21 +257,25 @@ __device__ __forceinline__ T facec(T an, T anb, T a_min)
 // reciprocal (FP64), then one residual correction of the quotient
 // (Markstein's method); within an ulp of the rounded quotient.  Every
 // Gauss-Seidel kernel of the smoother uses it, so they round identically.
-__device__ __forceinline__ float qdiv(float x, float d)
-{
-    const float r = __builtin_amdgcn_rcpf(d);
-    const float q = x * r;
-    return fmaf(fmaf(-d, q, x), r, q);
-}
+// The quotient in two parts, for a divisor used more than once: the (refined)
+// reciprocal, and the quotient from it.
+__device__ __forceinline__ float qrecip(float d) { return __builtin_amdgcn_rcpf(d); }
 
-__device__ __forceinline__ double qdiv(double x, double d)
+__device__ __forceinline__ double qrecip(double d)
 {
     double r = __builtin_amdgcn_rcp(d);
     r = fma(r, fma(-d, r, 1.0), r);
-    r = fma(r, fma(-d, r, 1.0), r);
-    const double q = x * r;
+    return fma(r, fma(-d, r, 1.0), r);
+}
+
+template <typename T>
+__device__ __forceinline__ T qdiv(T x, T d, T r)
+{
+    const T q = x * r;
     return fma(fma(-d, q, x), r, q);
 }
 
+__device__ __forceinline__ float qdiv(float x, float d) { return qdiv(x, d, qrecip(d)); }
+__device__ __forceinline__ double qdiv(double x, double d) { return qdiv(x, d, qrecip(d)); }
 
 }  // namespace recon

@@ -9,10 +9,7 @@ namespace recon {
 // `part` (capacity kPartCap doubles); reduce_finalize() then folds the rows
 // in a fixed order into out[0..K).  Results are bitwise reproducible for a
 // given launch shape.
-// The coarsest level's matrix follows `part`: (n^3/2)^2 entries in FP64 and in
-// FP32 up to n = 10, in doubles (a multiple of 32, so both stay aligned).
-constexpr long kCoarseMat = 375040;
-constexpr long kPartCap = (1L << 21) - kCoarseMat;
+constexpr long kPartCap = 1L << 21;
 
 // Device-resident scalars of the conjugate-gradient loop (8 doubles): the dot
 // products land here from the reductions, and the kernels that need the step
@@ -150,17 +147,22 @@ hipError_t launch_restrict(const T *f, T *c, int n, hipStream_t s);
 template <typename T>
 hipError_t launch_prolong_add(T *u, const T *e, int n, hipStream_t s);
 // The V-cycle from a level of edge n[0] <= 16 down (smallgrid.hip) in one
-// launch: n, scale and a of its levels, b and u of the first.  H is the
-// coarsest level's matrix, made by launch_coarse_matrix for the same a and
-// pairs (edges up to 10), or null: the level is relaxed pass by pass.
+// launch: n, scale and a of its levels, b and u of the first.
 constexpr int kTailLevels = 4;
 bool tail_supported(int n);
-bool coarse_matrix_supported(int n);
 template <typename T>
-hipError_t launch_coarse_matrix(const T *a, T *H, int n, T a_min, int pairs, hipStream_t s);
+hipError_t launch_tail(const T *const *a, const int *n, const T *scale, int levels, const T *b, T *u, T a_min,
+                       int n_pre, int n_post, int pairs, hipStream_t s);
+// A level's downward half (two sweeps from u = 0, red then black, and
+// c = R (b - scale A u)) and upward half (u_out = two sweeps, black then red,
+// of u_in + P e) in one launch each (smallgrid.hip); u_in distinct from u_out.
 template <typename T>
-hipError_t launch_tail(const T *const *a, const int *n, const T *scale, int levels, const T *b, T *u, const T *H,
-                       T a_min, int n_pre, int n_post, int pairs, hipStream_t s);
+bool tile_supported(int n);
+template <typename T>
+hipError_t launch_pre_tile(const T *a, const T *b, T *u, T *c, int n, T scale, T a_min, hipStream_t s);
+template <typename T>
+hipError_t launch_post_tile(const T *a, const T *b, const T *u_in, const T *e, T *u_out, int n, T scale, T a_min,
+                            hipStream_t s);
 hipError_t launch_cast_f32(const double *src, float *dst, long n3, hipStream_t s);
 hipError_t launch_cast_f64(const float *src, double *dst, long n3, hipStream_t s);
 

@@ -51,14 +51,13 @@ struct Levels {
     T *b[kMaxLevels];    // right-hand side (level 0: the caller's residual)
     T *res[kMaxLevels];  // residual inside the cycle
     T *tmp[kMaxLevels];  // second buffer for out-of-place sweeps
-    T *H = nullptr;      // the coarsest level's matrix (coarsest edges up to 10)
 };
 
 // Byte layout of the caller's workspace.  Computed identically by
 // recon_workspace_bytes and recon_init.
 struct Layout {
     size_t total = 0;
-    size_t part, H, scal;
+    size_t part, scal;
     size_t m, phi, M, t, b, u, r, z, p, q, dphi;
     size_t lv64_a[kMaxLevels], lv64_u[kMaxLevels], lv64_b[kMaxLevels], lv64_res[kMaxLevels], lv64_tmp[kMaxLevels];
     size_t lv32_a[kMaxLevels], lv32_u[kMaxLevels], lv32_b[kMaxLevels], lv32_res[kMaxLevels], lv32_tmp[kMaxLevels];
@@ -112,7 +111,6 @@ bool make_layout(int n, const recon_config *cfg, Layout &Lo)
     const size_t n3 = (size_t)n * n * n;
     const size_t f64 = n3 * 8;
     Lo.part = take(sizeof(double) * kPartCap);
-    Lo.H = take(sizeof(double) * kCoarseMat);
     Lo.scal = take(sizeof(double) * kScal);
     Lo.m = take(f64);
     Lo.phi = take(f64);
@@ -486,14 +484,16 @@ int collect_profile(recon_ctx *ctx, recon_stats *st)
     return RECON_OK;
 }
 
-// The coarsest level's relaxation as a product with its matrix: in FP32
-// always, in FP64 below 128^3, where it is a tenth of the V-cycle or more.
-// From 128^3 in FP64 the relaxation itself is 5% of the V-cycle or less, and
-// the product's other rounding would be all that changes there.
+// Levels whose down and up halves take one launch each (smallgrid.hip): their
+// halo's recomputation costs less than the launches it saves up to 64^3 in
+// FP64 and 80^3 in FP32, where two workgroups share a CU (whole solves, tiles
+// against single kernels: FP64 64^3 11.7 against 12.7 ms, 80^3 17.9 against
+// 17.3, 96^3 22.7 against 19.9; FP32 80^3 14.0 against 14.9, 96^3 equal,
+// 112^3 24.6 against 24.1).
 template <typename T>
-bool use_coarse_matrix(const Levels<T> &S)
+bool use_tiles(int n)
 {
-    return coarse_matrix_supported(S.n[S.L - 1]) && (sizeof(T) == 4 || S.n[0] < 128);
+    return n <= (sizeof(T) == 4 ? 80 : 64) && tile_supported<T>(n);
 }
 
 // out = V(rhs) on level l from a zero initial guess: n_pre sweeps red->black,
@@ -508,8 +508,16 @@ int vcycle(recon_ctx *ctx, Levels<T> &S, int l, const T *rhs, T *out)
         T sl[kTailLevels];
         const int levels = S.L - l;
         for (int q = 0; q < levels && q < kTailLevels; ++q) sl[q] = (T)level_scale(l + q);
-        HIPCHK(launch_tail<T>(S.a + l, S.n + l, sl, levels, rhs, out, use_coarse_matrix<T>(S) ? S.H : nullptr, amin,
-                              ctx->cfg.n_pre, ctx->cfg.n_post, ctx->cfg.coarse_sweeps, ctx->stream));
+        HIPCHK(launch_tail<T>(S.a + l, S.n + l, sl, levels, rhs, out, amin, ctx->cfg.n_pre, ctx->cfg.n_post,
+                              ctx->cfg.coarse_sweeps, ctx->stream));
+        return RECON_OK;
+    }
+    // the tiles do two sweeps from zero and two after the correction; timed
+    // sweeps (cfg.profile) are launches of their own
+    if (use_tiles<T>(n) && ctx->cfg.n_pre == 2 && ctx->cfg.n_post == 2 && !(l == 0 && ctx->prof)) {
+        HIPCHK(launch_pre_tile<T>(S.a[l], rhs, S.tmp[l], S.b[l + 1], n, sc, amin, ctx->stream));
+        TRY(vcycle<T>(ctx, S, l + 1, S.b[l + 1], S.u[l + 1]));
+        HIPCHK(launch_post_tile<T>(S.a[l], rhs, S.tmp[l], S.u[l + 1], out, n, sc, amin, ctx->stream));
         return RECON_OK;
     }
     T *cur = out, *alt = S.tmp[l];
@@ -528,16 +536,6 @@ int vcycle(recon_ctx *ctx, Levels<T> &S, int l, const T *rhs, T *out)
     return RECON_OK;
 }
 
-// The coarsest level's matrix of a built hierarchy, where the V-cycle uses it.
-template <typename T>
-int coarse_matrix(recon_ctx *ctx, Levels<T> &S)
-{
-    const int n = S.n[S.L - 1];
-    if (use_coarse_matrix<T>(S))
-        HIPCHK(launch_coarse_matrix<T>(S.a[S.L - 1], S.H, n, (T)ctx->cfg.a_min, ctx->cfg.coarse_sweeps, ctx->stream));
-    return RECON_OK;
-}
-
 // Coefficient hierarchy from a0 (= M): a_{l+1} = R a_l in FP64, and the FP32
 // copies when the V-cycle runs in FP32.
 int build_hierarchy(recon_ctx *ctx, const double *a0)
@@ -548,9 +546,8 @@ int build_hierarchy(recon_ctx *ctx, const double *a0)
     if (ctx->cfg.precision == RECON_MIXED) {
         for (int l = 0; l < S.L; ++l)
             HIPCHK(launch_cast_f32(S.a[l], ctx->L32.a[l], (long)S.n[l] * S.n[l] * S.n[l], ctx->stream));
-        return coarse_matrix<float>(ctx, ctx->L32);
     }
-    return coarse_matrix<double>(ctx, S);
+    return RECON_OK;
 }
 
 // z = V(r) in the configured precision (r FP64 in, z FP64 out for FP64 mode;
@@ -1062,8 +1059,6 @@ void bind_context(recon_ctx *ctx, int n, const recon_config *cfg, void *workspac
                              k0 + 6 * ctx->n3};
     }
     ctx->L64.L = ctx->L32.L = lo.levels;
-    ctx->L64.H = wsp<double>(ctx, lo.H);
-    ctx->L32.H = reinterpret_cast<float *>(ctx->L64.H + kCoarseMat / 3 * 2);
     int nl = n;
     for (int l = 0; l < lo.levels; ++l, nl /= 2) {
         ctx->L64.n[l] = ctx->L32.n[l] = nl;
@@ -1765,7 +1760,6 @@ int recon_stage_vcycle(recon_ctx *ctx, const void *a, const void *r, void *z, in
         Levels<float> &S = ctx->L32;
         HIPCHK(hipMemcpyAsync(S.a[0], a, n3 * 4, hipMemcpyDeviceToDevice, ctx->stream));
         for (int l = 0; l + 1 < S.L; ++l) HIPCHK(launch_restrict<float>(S.a[l], S.a[l + 1], S.n[l], ctx->stream));
-        TRY(coarse_matrix<float>(ctx, S));
         TRY(vcycle<float>(ctx, S, 0, (const float *)r, (float *)z));
     }
     HIPCHK(hipStreamSynchronize(ctx->stream));

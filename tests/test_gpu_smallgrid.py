@@ -49,3 +49,30 @@ def test_small_cycle_against_oracle(torch_cuda, n, cn, pre, post, pairs):
     assert rel(g, z) < 1e-12
     g = rec.vcycle(torch.from_numpy(a).float().cuda(), torch.from_numpy(r).float().cuda()).double().cpu().numpy()
     assert rel(g, z) < 1e-4
+
+
+@pytest.mark.parametrize("n,cn,dtype", [(20, 10, 64), (20, 10, 32), (24, 6, 64), (28, 14, 32), (32, 8, 64), (32, 8, 32),
+                                        (40, 10, 64), (48, 6, 64), (56, 14, 32), (64, 8, 64), (64, 8, 32), (80, 10, 32)])
+def test_tiles_equal_the_separate_kernels(torch_cuda, n, cn, dtype):
+    """A V-cycle whose finest level runs in two tile launches, against the
+    same cycle from the sweep, residual, restriction and prolongation kernels
+    of the stage calls around the V-cycle of the next level: bit for bit (the
+    level scale 1/4 is a power of two)."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    rng = np.random.default_rng(900 + n)
+    t = torch.float64 if dtype == 64 else torch.float32
+    a = torch.from_numpy(np.exp(2.0 * rng.normal(size=(n, n, n)))).cuda().to(t)
+    r = torch.from_numpy(rng.normal(size=(n, n, n))).cuda().to(t)
+    cfg = binding.Config(coarse_n=cn, precision=binding.MIXED)
+    rec = binding.Recon(n, cfg)
+    z = rec.vcycle(a, r)
+    u = torch.zeros_like(r)
+    for _ in range(2):
+        u = rec.rbgs(u, a, r, first=0, variant=1)
+    c = rec.residual_restrict(u, a, r, variant=1)
+    e = binding.Recon(n // 2, cfg).vcycle(rec.restrict(a, variant=1), 4.0 * c)
+    u = rec.prolong_add(u, e, variant=1)
+    for _ in range(2):
+        u = rec.rbgs(u, a, r, first=1, variant=1)
+    assert torch.equal(z, u)

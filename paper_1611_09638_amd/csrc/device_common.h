@@ -83,6 +83,66 @@ __device__ void block_reduce_store(double (&v)[K], double *part, int row)
     }
 }
 
+template <int OFF>
+__device__ __forceinline__ double lane_down(double v)  // lane i gets lane i + OFF of its 16
+{
+    union {
+        double d;
+        int w[2];
+    } x;
+    x.d = v;
+    x.w[0] = __builtin_amdgcn_update_dpp(0, x.w[0], 0x100 | OFF, 15, 15, true);
+    x.w[1] = __builtin_amdgcn_update_dpp(0, x.w[1], 0x100 | OFF, 15, 15, true);
+    return x.d;
+}
+
+// The sums of `rows` rows of K partials in the order of reduce_finalize (thread
+// t of 256 takes rows t, t + 256, ...; then a halving tree), formed by every
+// workgroup for itself.  Workgroups of 256 threads; every thread gets the sums.
+template <int K>
+__device__ __forceinline__ void fold_sums(const double *__restrict__ part, int rows, double (&out)[K])
+{
+    __shared__ double sm[K][256];
+    const int t = threadIdx.x + blockDim.x * (threadIdx.y + blockDim.y * threadIdx.z);
+    double x[K];
+#pragma unroll
+    for (int c = 0; c < K; ++c) x[c] = 0.0;
+    int r = t;
+    for (; r + 3 * 256 < rows; r += 4 * 256) {
+        double y[4][K];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int c = 0; c < K; ++c) y[v][c] = part[(size_t)(r + v * 256) * K + c];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int c = 0; c < K; ++c) x[c] += y[v][c];
+    }
+    for (; r < rows; r += 256)
+#pragma unroll
+        for (int c = 0; c < K; ++c) x[c] += part[(size_t)r * K + c];
+#pragma unroll
+    for (int c = 0; c < K; ++c) sm[c][t] = x[c];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+        double m[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) m[q] = sm[c][(t & 15) + 16 * q];
+#pragma unroll
+        for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+            for (int q = 0; q < h; ++q) m[q] += m[q + h];
+        double v = m[0];
+        v += lane_down<8>(v);
+        v += lane_down<4>(v);
+        v += lane_down<2>(v);
+        v += lane_down<1>(v);
+        out[c] = __shfl(v, 0, 64);
+    }
+}
+
 __device__ __forceinline__ int block_row()
 {
     return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);

@@ -32,7 +32,10 @@ struct Part {
     int k;          // partials per row
 };
 
-hipError_t reduce_finalize(const Part &p, const int *ops, double *out, hipStream_t s);
+// host != null (memory that the device can write): the launch also copies
+// `count` <= 256 doubles from `from` there, the new results among them.
+hipError_t reduce_finalize(const Part &p, const int *ops, double *out, hipStream_t s, const double *from = nullptr,
+                           double *host = nullptr, int count = 0);
 
 // ---------------------------------------------------------------- input
 hipError_t launch_check_input(const double *rho, long n3, Part &p, hipStream_t s);  // K=2: sum, bad count
@@ -216,11 +219,20 @@ hipError_t launch_update_p(const Z *z, double *pv, double beta, long n3, bool fi
 template <typename Z>
 hipError_t launch_update_pq(const Z *z, const double *a, double *pv, double *q, double beta, int n,
                             double a_min, bool first, const double *ks, Part &p, hipStream_t s);
+// p_new = z + beta p_old (first: z; beta from ks as above) and q = A p_new with
+// partial K=1 sum p_new.q in one gather launch; p_new distinct from p_old.
+// dots: with blocks > 0 the K=2 partials of z.r and z.q, folded by this launch
+// (into ks as well), else they are in ks already; p's rows go elsewhere.
+// Needs edges above 8 to fold.
+template <typename Z>
+hipError_t launch_direction(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
+                            double a_min, bool first, double *ks, const Part &dots, Part &p, hipStream_t s);
 // u += alpha p (if u != null); r -= alpha q; partial K=1: sum r^2; r32 = (float) r if r32 != null.
 // With ks != null: alpha = ks[KS_RZ] / ks[KS_PQ], and the kernel stores it in
-// ks[KS_ALPHA] and ks[KS_RZ] in ks[KS_RZ_OLD].
+// ks[KS_ALPHA] and ks[KS_RZ] in ks[KS_RZ_OLD].  pq with blocks > 0: the K=1
+// partials of p.q, folded by this launch in place of ks[KS_PQ].
 hipError_t launch_update_ur(double *u, double *r, const double *pv, const double *q, double alpha,
-                            float *r32, long n3, double *ks, Part &p, hipStream_t s);
+                            float *r32, long n3, double *ks, Part &p, hipStream_t s, const Part *pq = nullptr);
 // u += z (Z = double or float)
 template <typename Z>
 hipError_t launch_add_correction(double *u, const Z *z, long n3, hipStream_t s);

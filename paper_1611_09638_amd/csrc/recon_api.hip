@@ -185,6 +185,7 @@ struct recon_ctx {
     Part part;
     double *scal = nullptr;       // device scalars (reduction results)
     double *host_scal = nullptr;  // pinned host mirror
+    double *host_dev = nullptr;   // its device address (null: not writable from the device)
     double *m, *phi, *M, *t, *b, *u, *r, *z, *p, *q, *dphi;
     Levels<double> L64;
     Levels<float> L32;
@@ -245,12 +246,22 @@ T *wsp(recon_ctx *ctx, size_t off)
     return off == (size_t)-1 ? nullptr : reinterpret_cast<T *>(ctx->ws + off);
 }
 
+// Fold the partials of the last reducing launch into `out` and bring `count`
+// scalars from `from` to host_scal: by the folding launch itself where the
+// device can write there (pinned memory), else by a copy behind it.
+int finalize_to_host(recon_ctx *ctx, const int *ops, double *out, const double *from, int count)
+{
+    HIPCHK(reduce_finalize(ctx->part, ops, out, ctx->stream, from, ctx->host_dev, count));
+    if (!ctx->host_dev)
+        HIPCHK(hipMemcpyAsync(ctx->host_scal, from, sizeof(double) * count, hipMemcpyDeviceToHost, ctx->stream));
+    return RECON_OK;
+}
+
 // Fold the partials of the last reducing launch and read K scalars to the host.
 int fetch(recon_ctx *ctx, const int *ops, double *out)
 {
     const int K = ctx->part.k;
-    HIPCHK(reduce_finalize(ctx->part, ops, ctx->scal, ctx->stream));
-    HIPCHK(hipMemcpyAsync(ctx->host_scal, ctx->scal, sizeof(double) * K, hipMemcpyDeviceToHost, ctx->stream));
+    TRY(finalize_to_host(ctx, ops, ctx->scal, ctx->scal, K));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     for (int c = 0; c < K; ++c) out[c] = ctx->host_scal[c];
     return RECON_OK;
@@ -287,10 +298,12 @@ int wait_copy_end(recon_ctx *ctx)
     return RECON_OK;
 }
 
+// (also folds ||r||^2, the last reducing launch)
 int fetch_krylov_begin(recon_ctx *ctx)
 {
-    HIPCHK(hipMemcpyAsync(ctx->host_scal, ctx->scal + kKrylovScal, sizeof(double) * KS_COUNT,
-                          hipMemcpyDeviceToHost, ctx->stream));
+    static const int sum[1] = {RED_SUM};
+    double *ks = ctx->scal + kKrylovScal;
+    TRY(finalize_to_host(ctx, sum, ks + KS_RR, ks, KS_COUNT));
     return wait_copy_begin(ctx);
 }
 
@@ -312,9 +325,7 @@ int fetch_sum(recon_ctx *ctx, double *out)
 int fetch_sum1_begin(recon_ctx *ctx)
 {
     static const int ops[8] = {RED_SUM, RED_SUM, RED_SUM, RED_SUM, RED_SUM, RED_SUM, RED_SUM, RED_SUM};
-    HIPCHK(reduce_finalize(ctx->part, ops, ctx->scal, ctx->stream));
-    HIPCHK(hipMemcpyAsync(ctx->host_scal, ctx->scal, sizeof(double) * ctx->part.k, hipMemcpyDeviceToHost,
-                          ctx->stream));
+    TRY(finalize_to_host(ctx, ops, ctx->scal, ctx->scal, ctx->part.k));
     return wait_copy_begin(ctx);
 }
 
@@ -536,6 +547,12 @@ int vcycle(recon_ctx *ctx, Levels<T> &S, int l, const T *rhs, T *out)
     return RECON_OK;
 }
 
+// Grids whose reductions leave few enough partials (at most 14 per thread of a
+// folding workgroup, at 96^3) that each consumer folds them itself instead of
+// waiting for a folding launch (3-6 us): whole solves, FP64, 32^3 7.6 -> 7.0 ms,
+// 64^3 11.2 -> 10.5, 80^3 16.0 -> 15.5, 96^3 19.4 -> 19.2; 112^3 the same.
+bool fold_in_consumer(int n) { return n > 8 && n <= 96; }
+
 // Coefficient hierarchy from a0 (= M): a_{l+1} = R a_l in FP64, and the FP32
 // copies when the V-cycle runs in FP32.
 int build_hierarchy(recon_ctx *ctx, const double *a0)
@@ -632,7 +649,13 @@ int mg_solve(recon_ctx *ctx, const double *a0, const double *b, double tol, int 
         cycles = 1;
         if (mixed) HIPCHK(launch_dots_zr_zq<float>(ctx->L32.u[0], ctx->r, nullptr, n3, ctx->part, ctx->stream));
         else HIPCHK(launch_dots_zr_zq<double>(ctx->z, ctx->r, nullptr, n3, ctx->part, ctx->stream));
-        HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
+        // Small grids: the direction and the residual update fold the partials
+        // of the sums they need themselves (dots and pq, in separate halves of
+        // the partials), and the direction is one gather launch.
+        const bool small = !Kf && fold_in_consumer(n);
+        Part dots = ctx->part, pq = ctx->part;
+        pq.part = ctx->part.part + kPartCap / 2;
+        if (!small) HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
         bool first = true;
         // Streaming levels form the new direction out of place, fused with its
         // operator product; it alternates between p and t (idle during a solve),
@@ -670,6 +693,14 @@ int mg_solve(recon_ctx *ctx, const double *a0, const double *b, double tol, int 
                 if (mixed) HIPCHK(launch_update_p<float>(ctx->L32.u[0], pc, 0.0, n3, first, ks, ctx->stream));
                 else HIPCHK(launch_update_p<double>(ctx->z, pc, 0.0, n3, first, ks, ctx->stream));
                 HIPCHK(launch_full_apply_dot(*Kf, pc, ctx->q, n, ctx->cfg.a_min, ctx->part, ctx->stream));
+            } else if (small) {
+                if (mixed)
+                    HIPCHK(launch_direction<float>(ctx->L32.u[0], pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first, ks, dots,
+                                                   pq, ctx->stream));
+                else
+                    HIPCHK(launch_direction<double>(ctx->z, pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first, ks, dots, pq,
+                                                    ctx->stream));
+                std::swap(pc, pn);
             } else if (mixed) {
                 HIPCHK(launch_update_pq<float>(ctx->L32.u[0], a0, pc, ctx->q, 0.0, n, ctx->cfg.a_min, first, ks,
                                                ctx->part, ctx->stream));
@@ -678,11 +709,10 @@ int mg_solve(recon_ctx *ctx, const double *a0, const double *b, double tol, int 
                                                 ctx->stream));
             }
             first = false;
-            HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_PQ, ctx->stream));
+            if (!small) HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_PQ, ctx->stream));
             HIPCHK(launch_update_ur(stream ? nullptr : ctx->u, ctx->r, pc, ctx->q, 0.0, r32, n3, ks, ctx->part,
-                                    ctx->stream));
+                                    ctx->stream, small ? &pq : nullptr));
             due = stream;
-            HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RR, ctx->stream));
             // The stop test needs ||r|| on the host.  When this step cannot be
             // the last (a fixed count not yet reached, or the residual norm
             // extrapolated from the last two steps still well above the
@@ -709,7 +739,8 @@ int mg_solve(recon_ctx *ctx, const double *a0, const double *b, double tol, int 
             ++cycles;
             if (mixed) HIPCHK(launch_dots_zr_zq<float>(ctx->L32.u[0], ctx->r, ctx->q, n3, ctx->part, ctx->stream));
             else HIPCHK(launch_dots_zr_zq<double>(ctx->z, ctx->r, ctx->q, n3, ctx->part, ctx->stream));
-            HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
+            dots = ctx->part;
+            if (!small) HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
         }
         if (due && mixed) HIPCHK(launch_axpy(ctx->u, f32(pc), 0.0, n3, ctx->stream, ks + KS_ALPHA));
         else if (due) HIPCHK(launch_axpy(ctx->u, pc, 0.0, n3, ctx->stream, ks + KS_ALPHA));
@@ -1200,6 +1231,7 @@ int recon_init(recon_ctx **out, int n, const recon_config *cfg, void *workspace,
     bind_context(ctx, n, cfg, workspace, ws_bytes, hip_stream, lo);
     if (hipHostMalloc(reinterpret_cast<void **>(&ctx->host_scal), sizeof(double) * kScal, hipHostMallocDefault) !=
             hipSuccess ||
+        hipHostGetDevicePointer(reinterpret_cast<void **>(&ctx->host_dev), ctx->host_scal, 0) != hipSuccess ||
         hipEventCreate(&ctx->ev0) != hipSuccess || hipEventCreate(&ctx->ev1) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->ev_ks, hipEventDisableTiming) != hipSuccess) {
         recon_destroy(ctx);

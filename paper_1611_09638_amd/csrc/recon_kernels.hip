@@ -20,7 +20,10 @@ struct OpsK {
     int op[8];
 };
 
-__global__ void k_finalize(const double *__restrict__ part, int rows, int K, OpsK ops, double *__restrict__ out)
+// With host != null the launch also copies `count` doubles from `from` to host
+// memory that the device can write.
+__global__ void k_finalize(const double *__restrict__ part, int rows, int K, OpsK ops, double *out, const double *from,
+                           double *host, int count)
 {
     __shared__ double sm[256];
     const int t = threadIdx.x;
@@ -49,13 +52,15 @@ __global__ void k_finalize(const double *__restrict__ part, int rows, int K, Ops
         if (t == 0) out[c] = sm[0];
         __syncthreads();
     }
+    if (host && t < count) host[t] = from[t];
 }
 
-hipError_t reduce_finalize(const Part &p, const int *ops, double *out, hipStream_t s)
+hipError_t reduce_finalize(const Part &p, const int *ops, double *out, hipStream_t s, const double *from, double *host,
+                           int count)
 {
     OpsK o;
     for (int c = 0; c < 8; ++c) o.op[c] = c < p.k ? ops[c] : RED_SUM;
-    k_finalize<<<1, 256, 0, s>>>(p.part, p.blocks, p.k, o, out);
+    k_finalize<<<1, 256, 0, s>>>(p.part, p.blocks, p.k, o, out, from, host, count);
     return hipGetLastError();
 }
 
@@ -765,6 +770,71 @@ __global__ void k_apply_dot(const double *__restrict__ pv, const double *__restr
     block_reduce_store<1, RED_SUM>(v, part, block_row());
 }
 
+// p_new = z + beta p_old (first: z) and q = A p_new with sum p_new.q in one
+// launch: a node forms p_new at its six neighbours too, from fields that sit in
+// L2 on the grids this is for, and stores its own.  The values and the sums are
+// those of k_update_p and k_apply_dot, whose second launch this saves (32^3:
+// 2.9 + 3.9 us).  rows > 0: z.r and z.q are still partials of that many rows;
+// every workgroup folds them, and the first stores them in ks.
+template <typename Z, int FIRST>
+__global__ void k_direction(const Z *__restrict__ z, const double *__restrict__ p_old, double *__restrict__ p_new,
+                            const double *__restrict__ a, double *__restrict__ q, int n, int ipb, double a_min,
+                            double *part, const double *__restrict__ dots, int rows, double *ks)
+{
+    double beta = 0.0, d[2];
+    if (rows > 0) {
+        fold_sums<2>(dots, rows, d);
+        if (block_row() == 0 && threadIdx.x + threadIdx.y == 0) {
+            ks[KS_RZ] = d[0];
+            ks[KS_ZQ] = d[1];
+        }
+    } else {
+        d[1] = ks[KS_ZQ];
+    }
+    if (!FIRST) beta = -ks[KS_ALPHA] * d[1] / ks[KS_RZ_OLD];
+    auto pv = [&](size_t x) { return FIRST ? (double)z[x] : (double)z[x] + beta * p_old[x]; };
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = blockIdx.y * blockDim.y + threadIdx.y;
+    double v[1] = {0.0};
+    if (k < n && j < n) {
+        const int jp = wrapc(j + 1, n), jm = wrapc(j - 1, n), kp = wrapc(k + 1, n), km = wrapc(k - 1, n);
+        const int i0 = blockIdx.z * ipb, i1 = min(n, i0 + ipb);
+        for (int i = i0; i < i1; ++i) {
+            const int ip = wrapc(i + 1, n), im = wrapc(i - 1, n);
+            const size_t p = lin(i, j, k, n);
+            const double un = pv(p), an = a[p];
+            const size_t qq[6] = {lin(ip, j, k, n), lin(im, j, k, n), lin(i, jp, k, n),
+                                  lin(i, jm, k, n), lin(i, j, kp, n), lin(i, j, km, n)};
+            double acc = 0.0;
+#pragma unroll
+            for (int f = 0; f < 6; ++f) acc += facec(an, a[qq[f]], a_min) * (pv(qq[f]) - un);
+            p_new[p] = un;
+            q[p] = acc;
+            v[0] += un * acc;
+        }
+    }
+    block_reduce_store<1, RED_SUM>(v, part, block_row());
+}
+
+template <typename Z>
+hipError_t launch_direction(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
+                            double a_min, bool first, double *ks, const Part &dots, Part &p, hipStream_t s)
+{
+    Shape3 sh = shape3(n);
+    const int rows = dots.blocks;
+    if (p_new == p_old || (rows > 0 && (sh.block.x * sh.block.y != 256 || dots.k != 2 || dots.part == p.part)))
+        return hipErrorInvalidValue;
+    if (first)
+        k_direction<Z, 1><<<sh.grid, sh.block, 0, s>>>(z, p_old, p_new, a, q, n, sh.ipb, a_min, p.part, dots.part, rows,
+                                                       ks);
+    else
+        k_direction<Z, 0><<<sh.grid, sh.block, 0, s>>>(z, p_old, p_new, a, q, n, sh.ipb, a_min, p.part, dots.part, rows,
+                                                       ks);
+    p.blocks = rows_of(sh);
+    p.k = 1;
+    return hipGetLastError();
+}
+
 template <typename Z>
 hipError_t launch_update_pq(const Z *z, const double *a, double *pv, double *q, double beta, int n, double a_min,
                             bool first, const double *ks, Part &p, hipStream_t s)
@@ -795,12 +865,16 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 template <bool U>
 __global__ void k_update_ur(double *__restrict__ u, double *__restrict__ r, const double *__restrict__ pv,
                             const double *__restrict__ q, double alpha, float *__restrict__ r32, long n3, double *part,
-                            double *ks)
+                            double *ks, const double *__restrict__ pq, int rows)
 {
     if (ks) {
         const double rz = ks[KS_RZ];
-        alpha = rz / ks[KS_PQ];
-        // only this kernel's other lanes read ks, and only KS_RZ and KS_PQ
+        double d[1];
+        if (rows > 0) fold_sums<1>(pq, rows, d);
+        else d[0] = ks[KS_PQ];
+        alpha = rz / d[0];
+        // only this kernel's other lanes read ks, and only KS_RZ and (without
+        // rows) KS_PQ
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             ks[KS_ALPHA] = alpha;
             ks[KS_RZ_OLD] = rz;
@@ -860,8 +934,10 @@ __global__ void k_update_ur(double *__restrict__ u, double *__restrict__ r, cons
 }
 
 hipError_t launch_update_ur(double *u, double *r, const double *pv, const double *q, double alpha, float *r32, long n3,
-                            double *ks, Part &p, hipStream_t s)
+                            double *ks, Part &p, hipStream_t s, const Part *pq)
 {
+    const int rows = pq ? pq->blocks : 0;
+    if (rows > 0 && (!ks || pq->k != 1 || pq->part == p.part)) return hipErrorInvalidValue;
     // the paired accesses need 16-byte aligned fields
     if ((reinterpret_cast<uintptr_t>(r) | reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(u) |
          reinterpret_cast<uintptr_t>(pv)) % 16 ||
@@ -870,8 +946,8 @@ hipError_t launch_update_ur(double *u, double *r, const double *pv, const double
     // up to 16384 workgroups (measured 755 against 813 us at 512^3 with 8192)
     const long pairs = (n3 + 1) / 2;
     const int nb = (int)std::min<long>((pairs + 255) / 256, 16384);
-    if (u) k_update_ur<true><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks);
-    else k_update_ur<false><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks);
+    if (u) k_update_ur<true><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, rows ? pq->part : nullptr, rows);
+    else k_update_ur<false><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, rows ? pq->part : nullptr, rows);
     p.blocks = nb;
     p.k = 1;
     return hipGetLastError();
@@ -901,6 +977,8 @@ hipError_t launch_add_correction(double *u, const Z *z, long n3, hipStream_t s)
     template hipError_t launch_dots_zr_zq<T>(const T *, const double *, const double *, long, Part &, hipStream_t); \
     template hipError_t launch_update_pq<T>(const T *, const double *, double *, double *, double, int, double,     \
                                             bool, const double *, Part &, hipStream_t);                           \
+    template hipError_t launch_direction<T>(const T *, const double *, double *, const double *, double *, int,     \
+                                            double, bool, double *, const Part &, Part &, hipStream_t);            \
     template hipError_t launch_update_p<T>(const T *, double *, double, long, bool, const double *, hipStream_t);  \
     template hipError_t launch_add_correction<T>(double *, const T *, long, hipStream_t);                        \
 

@@ -183,19 +183,6 @@ struct TailNodes {
     }
 };
 
-template <int OFF>
-__device__ __forceinline__ double lane_down(double v)  // lane i gets lane i + OFF of its 16
-{
-    union {
-        double d;
-        int w[2];
-    } x;
-    x.d = v;
-    x.w[0] = __builtin_amdgcn_update_dpp(0, x.w[0], 0x100 | OFF, 15, 15, true);
-    x.w[1] = __builtin_amdgcn_update_dpp(0, x.w[1], 0x100 | OFF, 15, 15, true);
-    return x.d;
-}
-
 // Mean of the N^3 values of x (natural order), by halving: thread t of 1024
 // takes x[t], x[t + 1024], ..., and a tree folds the threads (lanes 0-15 of the
 // first wave read the 1024 words and keep the tree's order).  red: 1024

@@ -76,3 +76,26 @@ def test_tiles_equal_the_separate_kernels(torch_cuda, n, cn, dtype):
     for _ in range(2):
         u = rec.rbgs(u, a, r, first=1, variant=1)
     assert torch.equal(z, u)
+
+
+@pytest.mark.parametrize("n,cn,dtype", [(10, 10, 64), (16, 8, 64), (16, 8, 32), (48, 6, 64), (64, 8, 32), (96, 6, 64),
+                                        (112, 14, 64)])
+def test_krylov_steps_on_small_grids(torch_cuda, n, cn, dtype):
+    """The conjugate-gradient loop at the edges of the grids whose consumers
+    fold the partial sums (10^3 and 96^3; 112^3 folds them in a launch): a
+    fixed number of steps against the oracle's solution at the same tolerance,
+    to the conditioning of the input times the solve's tolerance (contrast
+    below 100, tol 1e-12)."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    rng = np.random.default_rng(1200 + n)
+    a = np.exp(0.7 * rng.normal(size=(n, n, n)))
+    b = rng.normal(size=(n, n, n))
+    b -= b.mean()
+    u, cycles, _ = orc.mg_solve(a, b, orc.Config(coarse_n=cn, tol=1e-12))
+    rec = binding.Recon(n, binding.Config(coarse_n=cn, precision=binding.FP64 if dtype == 64 else binding.MIXED))
+    g, cyc, res = rec.mg_solve(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda(), tol=1e-12)
+    assert res <= 1e-12
+    assert rel(g.cpu().numpy(), u) < 1e-9
+    if dtype == 64:
+        assert cyc == cycles

@@ -48,18 +48,21 @@ hipError_t launch_cic(const float *pos, long long np, int n, double box, double 
 // ------------------------------------------------------- outer-step kernels
 // M = det(I + H) * CIC(m)(x); partial K=1: sum M
 hipError_t launch_meshmass(const double *phi, const double *m, double *M, int n, Part &p, hipStream_t s);
-// t = Sigma + C + E; partials K=2: sum Sigma^2, sum t
-hipError_t launch_source(const double *phi, const double *M, double rho_bar, double xi_m, double v_m, double *t, int n,
-                         Part &p, hipStream_t s);
-// out = c0 f + (1-c0)/6 sum nb - sub
-hipError_t launch_smooth(const double *f, double *out, int n, double c0, double sub, hipStream_t s);
+// Means are formed where they are used, from a sum over the grid in device
+// memory (*sum / n^3), so no launch waits for the host.
+// t = Sigma + C + E with Sigma = mean(M) - M, sum_M the sum of M; partials
+// K=2: sum Sigma^2, sum t
+hipError_t launch_source(const double *phi, const double *M, const double *sum_M, double xi_m, double v_m, double *t,
+                         int n, Part &p, hipStream_t s);
+// out = c0 f + (1-c0)/6 sum nb - mean of `sum` (null: 0)
+hipError_t launch_smooth(const double *f, double *out, int n, double c0, const double *sum, hipStream_t s);
 // the same three passes with the stencil field streamed through LDS (outer25.hip);
 // n a multiple of 64; the same node values, the partial sums grouped per workgroup
 bool outer25_supported(int n);
 hipError_t launch_meshmass25(const double *phi, const double *m, double *M, int n, Part &p, hipStream_t s);
-hipError_t launch_source25(const double *phi, const double *M, double rho_bar, double xi_m, double v_m, double *t,
+hipError_t launch_source25(const double *phi, const double *M, const double *sum_M, double xi_m, double v_m, double *t,
                            int n, Part &p, hipStream_t s);
-hipError_t launch_smooth25(const double *f, double *out, int n, double c0, double sub, hipStream_t s);
+hipError_t launch_smooth25(const double *f, double *out, int n, double c0, const double *sum, hipStream_t s);
 // partial K=1 (max): max_a |D_c f|
 hipError_t launch_max_shift(const double *f, int n, Part &p, hipStream_t s);
 // partial K=ntrial (sum): nodes where I + Hess(phi + 2^-j dphi) is not PD, j = j0..j0+ntrial-1;
@@ -122,7 +125,8 @@ hipError_t launch_deposit_adj(const double *xi, long long np, int n, const doubl
 template <typename X>
 hipError_t launch_axpy(double *y, const X *x, double alpha, long n3, hipStream_t s,
                        const double *alpha_dev = nullptr);
-hipError_t launch_add_scalar(double *y, const double *c_dev, double sign, double scale, long n3, hipStream_t s);
+// y += sign * (*sum / n3)
+hipError_t launch_add_mean(double *y, const double *sum, double sign, long n3, hipStream_t s);
 // delta = -L7 phi; phi_out = phi * h2 (if non-null); partials K=3: min det, min lambda0, max delta
 hipError_t launch_output(const double *phi, double *delta, double *phi_out, double h2, int n, Part &p,
                          hipStream_t s);
@@ -243,7 +247,7 @@ hipError_t launch_smooth_scaled(const double *f, double *out, int n, double c0, 
 hipError_t launch_coefgrad(const double *lam, const double *u, const double *M, double a_min, double *Mbar, int n,
                            hipStream_t s);
 // hb: 6 fields (xx, yy, zz, xy, xz, yz); partial K=1: sum of Sigmabar
-hipError_t launch_source_adj(const double *phi, const double *M, double rho_bar, const double *tbar, double xi_m,
+hipError_t launch_source_adj(const double *phi, const double *M, const double *sum_M, const double *tbar, double xi_m,
                              double v_m, double *Mbar, double *hb, int n, Part &p, hipStream_t s);
 // xb: 3 fields; mbar accumulated with atomics
 hipError_t launch_meshmass_adj(const double *phi, const double *m, const double *Mbar, double *hb, double *xb,

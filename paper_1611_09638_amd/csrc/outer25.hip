@@ -43,8 +43,10 @@ struct OuterArgs {
     const double *m;     // meshmass: the normalised density
     const double *M;     // source: the mass per cell
     double *out;         // M, t or the smoothed field
-    double rho_bar, xi_m, v_m;
-    double c0, cn, sv;   // smoothing: centre weight, neighbour weight, subtracted constant
+    const double *sum;   // source: the sum of M; smoothing: the sum whose mean is subtracted (null: 0)
+    double n3;           // nodes
+    double xi_m, v_m;
+    double c0, cn;       // smoothing: centre weight, neighbour weight
 };
 
 template <int MODE, int TJ, int TK, int NT>
@@ -95,6 +97,7 @@ __global__ void __launch_bounds__(NT) k_outer25(const double *__restrict__ f, in
         for (int r = 0; r < LU; ++r) P[dstL[r]] = rf[set][r];
     };
 
+    const double mean = A.sum ? *A.sum / A.n3 : 0.0;
     double v[K];
 #pragma unroll
     for (int c = 0; c < K; ++c) v[c] = 0.0;
@@ -107,7 +110,7 @@ __global__ void __launch_bounds__(NT) k_outer25(const double *__restrict__ f, in
             const size_t g = (size_t)p * n2 + gN[r];
             if constexpr (MODE == OUT_SMOOTH) {
                 const double nb = Pp[c] + Pm[c] + Pc[c + W] + Pc[c - W] + Pc[c + 1] + Pc[c - 1];
-                __builtin_nontemporal_store(A.c0 * Pc[c] + A.cn * nb - A.sv, &A.out[g]);
+                __builtin_nontemporal_store(A.c0 * Pc[c] + A.cn * nb - mean, &A.out[g]);
             } else {
                 Stencil19 s;
                 s.c = Pc[c];
@@ -157,7 +160,7 @@ __global__ void __launch_bounds__(NT) k_outer25(const double *__restrict__ f, in
                     A.out[g] = Mv;
                     v[0] += Mv;
                 } else {
-                    const double sigma = A.rho_bar - A.M[g];
+                    const double sigma = mean - A.M[g];
                     const double C = compression_limiter(e, A.xi_m);
                     const double E = gdet > A.v_m ? -2.0 * fabs(sigma) : 0.0;
                     const double tv = sigma + C + E;
@@ -229,25 +232,27 @@ hipError_t launch_meshmass25(const double *phi, const double *m, double *M, int 
     return launch_outer25<OUT_MESHMASS>(phi, n, A, &p, s);
 }
 
-hipError_t launch_source25(const double *phi, const double *M, double rho_bar, double xi_m, double v_m, double *t,
+hipError_t launch_source25(const double *phi, const double *M, const double *sum_M, double xi_m, double v_m, double *t,
                            int n, Part &p, hipStream_t s)
 {
     OuterArgs A{};
     A.M = M;
     A.out = t;
-    A.rho_bar = rho_bar;
+    A.sum = sum_M;
+    A.n3 = (double)((long)n * n * n);
     A.xi_m = xi_m;
     A.v_m = v_m;
     return launch_outer25<OUT_SOURCE>(phi, n, A, &p, s);
 }
 
-hipError_t launch_smooth25(const double *f, double *out, int n, double c0, double sub, hipStream_t s)
+hipError_t launch_smooth25(const double *f, double *out, int n, double c0, const double *sum, hipStream_t s)
 {
     OuterArgs A{};
     A.out = out;
     A.c0 = c0;
     A.cn = (1.0 - c0) / 6.0;
-    A.sv = sub;
+    A.sum = sum;
+    A.n3 = (double)((long)n * n * n);
     return launch_outer25<OUT_SMOOTH>(f, n, A, nullptr, s);
 }
 

@@ -158,13 +158,14 @@ __device__ void eigvec_sym(const Sym3 &e, double lam, double v[3])
 // Source adjoint.  tbar -> Sigmabar = tbar (1 - 2 [det e > v_m] sign Sigma),
 // Mbar -= Sigmabar (the mean(M) part is added afterwards from the partial
 // sums), lambda_0bar = tbar dC/dlambda_0 -> ebar = lambda_0bar v v^T.
-__global__ void k_source_adj(const double *__restrict__ phi, const double *__restrict__ M, double rho_bar,
-                             const double *__restrict__ tbar, double xi_m, double v_m, double *__restrict__ Mbar,
+__global__ void k_source_adj(const double *__restrict__ phi, const double *__restrict__ M,
+                             const double *__restrict__ sum_M, const double *__restrict__ tbar, double xi_m, double v_m, double *__restrict__ Mbar,
                              double *__restrict__ hb, int n, int ipb, double *part)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y * blockDim.y + threadIdx.y;
     const size_t n3 = (size_t)n * n * n;
+    const double rho_bar = *sum_M / (double)n3;
     double v1[1] = {0.0};
     if (k < n && j < n) {
         const int i0 = blockIdx.z * ipb, i1 = min(n, i0 + ipb);
@@ -201,11 +202,11 @@ __global__ void k_source_adj(const double *__restrict__ phi, const double *__res
     block_reduce_store<1, RED_SUM>(v1, part, block_row());
 }
 
-hipError_t launch_source_adj(const double *phi, const double *M, double rho_bar, const double *tbar, double xi_m,
+hipError_t launch_source_adj(const double *phi, const double *M, const double *sum_M, const double *tbar, double xi_m,
                              double v_m, double *Mbar, double *hb, int n, Part &p, hipStream_t s)
 {
     Shape3 sh = shape3(n);
-    k_source_adj<<<sh.grid, sh.block, 0, s>>>(phi, M, rho_bar, tbar, xi_m, v_m, Mbar, hb, n, sh.ipb, p.part);
+    k_source_adj<<<sh.grid, sh.block, 0, s>>>(phi, M, sum_M, tbar, xi_m, v_m, Mbar, hb, n, sh.ipb, p.part);
     p.blocks = rows_of(sh);
     p.k = 1;
     return hipGetLastError();

@@ -278,7 +278,6 @@ constexpr int kKrylovScal = 32;
 // The next V-cycle is queued ahead of the stop test while the extrapolated
 // residual norm is above this multiple of the target.
 constexpr double kAheadMargin = 8.0;
-static_assert(kKrylovScal + KS_COUNT <= kScal, "the scalar block fits");
 
 // In two halves, so that work queued between them overlaps the round trip:
 // the copy is enqueued with an event behind it, and the host later waits for
@@ -312,6 +311,42 @@ int fetch_krylov_end(recon_ctx *ctx, double *out)
     TRY(wait_copy_end(ctx));
     for (int c = 0; c < KS_COUNT; ++c) out[c] = ctx->host_scal[c];
     return RECON_OK;
+}
+
+// Scalars of a step that stay on the device: the launches that need one read
+// it there, and the host reads the whole block where it takes a decision (start
+// of the linear solve, step control).
+enum StepScalar {
+    ST_M = 0,     // sum of M
+    ST_SIG2 = 1,  // sum of Sigma^2
+    ST_T = 2,     // sum of the source (written with ST_SIG2)
+    ST_LOST = 3,  // particles not located
+    ST_BB = 4,    // b . b
+    ST_RR0 = 5,   // squared norm of the warm start's residual
+    ST_U = 6,     // sum of a solution
+    ST_RR = 7,    // squared norm of the solution's residual
+    ST_SHIFT = 8, // largest shift of a node
+    ST_COUNT = 9
+};
+constexpr int kStepScal = 48;  // their place in ctx->scal
+static_assert(kKrylovScal + KS_COUNT <= kStepScal && kStepScal + ST_COUNT <= kScal, "the scalar block fits");
+
+double *step_scal(recon_ctx *ctx, int which) { return ctx->scal + kStepScal + which; }
+
+// Fold the partials of the last reducing launch into a step scalar (two
+// partials: into it and the next); with `read` the host's copy of the block is
+// written behind it.
+int fold_step(recon_ctx *ctx, int which, bool read = false, int op = RED_SUM)
+{
+    const int ops[2] = {op, op};
+    if (read) return finalize_to_host(ctx, ops, step_scal(ctx, which), step_scal(ctx, 0), ST_COUNT);
+    HIPCHK(reduce_finalize(ctx->part, ops, step_scal(ctx, which), ctx->stream));
+    return RECON_OK;
+}
+
+void read_step(recon_ctx *ctx, double *v)
+{
+    for (int c = 0; c < ST_COUNT; ++c) v[c] = ctx->host_scal[c];
 }
 
 int fetch_sum(recon_ctx *ctx, double *out)
@@ -448,17 +483,18 @@ hipError_t meshmass_pass(const double *phi, const double *m, double *M, int n, P
     return launch_meshmass(phi, m, M, n, p, s);
 }
 
-hipError_t source_pass(const double *phi, const double *M, double rho_bar, double xi_m, double v_m, double *t, int n,
+hipError_t source_pass(const double *phi, const double *M, const double *sum_M, double xi_m, double v_m, double *t, int n,
                        Part &p, hipStream_t s, int variant = 0)
 {
-    if (use_outer_stream(n, variant)) return launch_source25(phi, M, rho_bar, xi_m, v_m, t, n, p, s);
-    return launch_source(phi, M, rho_bar, xi_m, v_m, t, n, p, s);
+    if (use_outer_stream(n, variant)) return launch_source25(phi, M, sum_M, xi_m, v_m, t, n, p, s);
+    return launch_source(phi, M, sum_M, xi_m, v_m, t, n, p, s);
 }
 
-hipError_t smooth_pass(const double *f, double *out, int n, double c0, double sub, hipStream_t s, int variant = 0)
+hipError_t smooth_pass(const double *f, double *out, int n, double c0, const double *sum, hipStream_t s,
+                       int variant = 0)
 {
-    if (use_outer_stream(n, variant)) return launch_smooth25(f, out, n, c0, sub, s);
-    return launch_smooth(f, out, n, c0, sub, s);
+    if (use_outer_stream(n, variant)) return launch_smooth25(f, out, n, c0, sum, s);
+    return launch_smooth(f, out, n, c0, sum, s);
 }
 
 // r = b - A u on the fine level in FP64, its squared norm, and optionally r
@@ -582,27 +618,59 @@ int precondition(recon_ctx *ctx)
 // the mass map, K = M e^-1 filled by the caller), still preconditioned by the
 // x ~ xi V-cycle of the built hierarchy (the caller builds it on K's mean
 // diagonal).
-int mg_solve(recon_ctx *ctx, const double *a0, const double *b, double tol, int *cycles_out, double *rel_out,
-             bool warm = false, const MassTensor *Kf = nullptr)
+//
+// Three parts: mg_start queues the norms, the first residual and the first
+// V-cycle; mg_wait waits for the step scalars queued so far (the norms among
+// them); mg_run does the rest and leaves ||b - A u||^2 in ST_RR and in the
+// host's block, for after the stream is drained.
+int mg_residual_from_zero(recon_ctx *ctx, const double *a0, const double *b, const MassTensor *Kf)
+{
+    // u = 0, so the residual kernel gives r = b
+    float *r32 = ctx->cfg.precision == RECON_MIXED ? ctx->L32.b[0] : nullptr;
+    HIPCHK(launch_zero(ctx->u, ctx->n3 * 8, ctx->stream));
+    HIPCHK(residual_norm(ctx, ctx->u, a0, b, ctx->r, r32, Kf));
+    return RECON_OK;
+}
+
+int mg_start(recon_ctx *ctx, const double *a0, const double *b, bool warm = false, const MassTensor *Kf = nullptr)
+{
+    float *r32 = ctx->cfg.precision == RECON_MIXED ? ctx->L32.b[0] : nullptr;
+    HIPCHK(launch_dot(b, b, ctx->n3, ctx->part, ctx->stream));
+    TRY(fold_step(ctx, ST_BB, !warm));
+    if (warm) {
+        HIPCHK(residual_norm(ctx, ctx->u, a0, b, ctx->r, r32, Kf));
+        TRY(fold_step(ctx, ST_RR0, true));
+    }
+    TRY(wait_copy_begin(ctx));
+    if (!warm) TRY(mg_residual_from_zero(ctx, a0, b, Kf));
+    // The first V-cycle, ahead of the host's look at the norms: it writes only z
+    // and the level scratch, so where it turns out not to be wanted (a zero
+    // right-hand side, a warm start not taken) it costs its time and changes
+    // nothing.  (Not with timed sweeps, whose count it would change.)
+    if (!ctx->prof) TRY(precondition(ctx));
+    return RECON_OK;
+}
+
+int mg_wait(recon_ctx *ctx, double *v)
+{
+    TRY(wait_copy_end(ctx));
+    read_step(ctx, v);
+    return RECON_OK;
+}
+
+int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const double *step, int *cycles_out,
+           int *status_out, bool warm = false, const MassTensor *Kf = nullptr)
 {
     const int n = ctx->n;
     const long n3 = ctx->n3;
     const bool mixed = ctx->cfg.precision == RECON_MIXED;
     float *r32 = mixed ? ctx->L32.b[0] : nullptr;
     double v[KS_COUNT];
-    HIPCHK(launch_dot(b, b, n3, ctx->part, ctx->stream));
-    TRY(fetch_sum(ctx, v));
-    const double bn = std::sqrt(v[0]);
-    bool started = false;
-    if (warm && bn > 0.0) {
-        HIPCHK(residual_norm(ctx, ctx->u, a0, b, ctx->r, r32, Kf));
-        TRY(fetch_sum(ctx, v));
-        started = std::sqrt(v[0]) < bn;
-    }
-    if (!started) {
-        // u = 0, so the residual kernel gives r = b
-        HIPCHK(launch_zero(ctx->u, n3 * 8, ctx->stream));
-        HIPCHK(residual_norm(ctx, ctx->u, a0, b, ctx->r, r32, Kf));
+    const double bn = std::sqrt(step[ST_BB]);
+    bool ready = !ctx->prof;  // z = V(r) is queued
+    if (warm && !(bn > 0.0 && std::sqrt(step[ST_RR0]) < bn)) {
+        TRY(mg_residual_from_zero(ctx, a0, b, Kf));
+        ready = false;
     }
     int cycles = 0;
     int status = RECON_E_NO_CONVERGENCE;
@@ -615,7 +683,7 @@ int mg_solve(recon_ctx *ctx, const double *a0, const double *b, double tol, int 
         // As in the Krylov loop below, the next V-cycle is queued ahead of the
         // stop test when this cycle cannot be the last; it writes only z and
         // the level scratch, and u changes only in the correction after it.
-        bool queued = false;
+        bool queued = ready;
         double rn_last = 0.0, rn_next = 0.0;
         for (int c = 1; c <= max_cycles; ++c) {
             cycles = c;
@@ -645,7 +713,7 @@ int mg_solve(recon_ctx *ctx, const double *a0, const double *b, double tol, int 
         // host), so the host waits once per step, for its stop test.
         double *ks = ctx->scal + kKrylovScal;
         static const int sums[2] = {RED_SUM, RED_SUM};
-        TRY(precondition(ctx));
+        if (!ready) TRY(precondition(ctx));
         cycles = 1;
         if (mixed) HIPCHK(launch_dots_zr_zq<float>(ctx->L32.u[0], ctx->r, nullptr, n3, ctx->part, ctx->stream));
         else HIPCHK(launch_dots_zr_zq<double>(ctx->z, ctx->r, nullptr, n3, ctx->part, ctx->stream));
@@ -747,18 +815,42 @@ int mg_solve(recon_ctx *ctx, const double *a0, const double *b, double tol, int 
     }
     // mean-free solution, then the true residual
     HIPCHK(launch_sum(ctx->u, n3, ctx->part, ctx->stream));
-    TRY(fetch_sum(ctx, v));
-    HIPCHK(launch_fill(ctx->scal + 16, 1, v[0] / (double)n3, ctx->stream));
-    HIPCHK(launch_add_scalar(ctx->u, ctx->scal + 16, -1.0, 1.0, n3, ctx->stream));
+    TRY(fold_step(ctx, ST_U));
+    HIPCHK(launch_add_mean(ctx->u, step_scal(ctx, ST_U), -1.0, n3, ctx->stream));
     HIPCHK(residual_norm(ctx, ctx->u, a0, b, ctx->r, nullptr, Kf));
-    TRY(fetch_sum(ctx, v));
-    const double rel = bn > 0.0 ? std::sqrt(v[0]) / bn : 0.0;
-    if (cycles_out) *cycles_out = cycles;
-    if (rel_out) *rel_out = rel;
-    if (status != RECON_OK)
-        return fail(ctx, RECON_E_NO_CONVERGENCE, "linear solve did not reach tol %.3g in %d V-cycles (rel %.3g)", tol,
-                    cycles, rel);
+    TRY(fold_step(ctx, ST_RR, true));
+    *cycles_out = cycles;
+    *status_out = status;
     return RECON_OK;
+}
+
+double mg_relative(const double *step)
+{
+    return step[ST_BB] > 0.0 ? std::sqrt(step[ST_RR]) / std::sqrt(step[ST_BB]) : 0.0;
+}
+
+int mg_failed(recon_ctx *ctx, double tol, int cycles)
+{
+    double v[ST_COUNT];
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    read_step(ctx, v);
+    return fail(ctx, RECON_E_NO_CONVERGENCE, "linear solve did not reach tol %.3g in %d V-cycles (rel %.3g)", tol,
+                cycles, mg_relative(v));
+}
+
+int mg_solve(recon_ctx *ctx, const double *a0, const double *b, double tol, int *cycles_out, double *rel_out,
+             const MassTensor *Kf = nullptr)
+{
+    double v[ST_COUNT];
+    int cycles = 0, status = RECON_OK;
+    TRY(mg_start(ctx, a0, b, false, Kf));
+    TRY(mg_wait(ctx, v));
+    TRY(mg_run(ctx, a0, b, tol, v, &cycles, &status, false, Kf));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    read_step(ctx, v);
+    if (cycles_out) *cycles_out = cycles;
+    if (rel_out) *rel_out = mg_relative(v);
+    return status == RECON_OK ? RECON_OK : mg_failed(ctx, tol, cycles);
 }
 
 // ------------------------------------------------------------ step control
@@ -774,14 +866,19 @@ hipError_t pd_trials(recon_ctx *ctx, const double *phi, const double *dphi, int 
     return launch_pd_trials(phi, dphi, ctx->n, j0, ntrial, ctx->part, ctx->stream, M, D);
 }
 
+// (step, if not null, receives the step scalars, all queued before the call
+// among them)
 int choose_step(recon_ctx *ctx, const double *phi, const double *dphi, double *alpha_out,
-                const double *M = nullptr, const double *D = nullptr, int *limit_out = nullptr)
+                const double *M = nullptr, const double *D = nullptr, int *limit_out = nullptr,
+                double *step = nullptr)
 {
-    static const int opmax[1] = {RED_MAX};
-    double v[8];
+    double v[ST_COUNT];
     HIPCHK(launch_max_shift(dphi, ctx->n, ctx->part, ctx->stream));
-    TRY(fetch(ctx, opmax, v));
-    const double shift = v[0];
+    TRY(fold_step(ctx, ST_SHIFT, true, RED_MAX));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    read_step(ctx, v);
+    if (step) std::copy(v, v + ST_COUNT, step);
+    const double shift = v[ST_SHIFT];
     if (!std::isfinite(shift)) return fail(ctx, RECON_E_NO_CONVERGENCE, "non-finite increment");
     int j0 = 0;
     while (j0 <= ctx->cfg.max_halvings && std::ldexp(1.0, -j0) * shift > ctx->cfg.s_max) ++j0;
@@ -822,22 +919,20 @@ int normalize(recon_ctx *ctx, const double *rho, double *m, double *mean_out)
 // go into their own buffer (ctx->shifts), which the reverse mode reads.
 int deposit_particles(recon_ctx *ctx)
 {
-    double v[1];
     HIPCHK(launch_invert_map(ctx->phi, ctx->part_pos, ctx->part_np, ctx->n, ctx->box, ctx->xi, ctx->shifts,
                              kInvertIters, kInvertTol, ctx->part, ctx->stream));
-    TRY(fetch_sum(ctx, v));
-    if (v[0] != 0.0)
-        return fail(ctx, RECON_E_NO_CONVERGENCE, "%.0f particles not located on the deformed mesh", v[0]);
+    TRY(fold_step(ctx, ST_LOST));
     HIPCHK(launch_deposit_xi(ctx->xi, ctx->part_np, ctx->n, ctx->M, ctx->stream));
     return RECON_OK;
 }
 
-// rho_bar = mean(M), rms(Sigma) and the source for the current phi; M is
-// gathered on the deformed mesh when `gather` (or, in a particle-deposit solve,
-// deposited from the particles), else (mass update) kept.
-int mass_state(recon_ctx *ctx, double *rho_bar, double *rms, double *mean_t, bool gather = true)
+// The mass and the source for the current phi, queued with their sums (ST_M,
+// ST_SIG2, ST_T, and ST_LOST in a particle-deposit solve); M is gathered on
+// the deformed mesh when `gather` (or, in a particle-deposit solve, deposited
+// from the particles), else (mass update) kept.  With `read` the host's copy
+// of the step scalars is written last.
+int queue_mass_state(recon_ctx *ctx, bool gather, bool read = false)
 {
-    double v[2];
     if (ctx->part_pos) {
         TRY(deposit_particles(ctx));
         HIPCHK(launch_sum(ctx->M, ctx->n3, ctx->part, ctx->stream));
@@ -846,13 +941,19 @@ int mass_state(recon_ctx *ctx, double *rho_bar, double *rms, double *mean_t, boo
     } else {
         HIPCHK(launch_sum(ctx->M, ctx->n3, ctx->part, ctx->stream));
     }
-    TRY(fetch_sum(ctx, v));
-    *rho_bar = v[0] / (double)ctx->n3;
-    HIPCHK(source_pass(ctx->phi, ctx->M, *rho_bar, ctx->cfg.xi_m, ctx->cfg.v_m, ctx->t, ctx->n, ctx->part,
-                         ctx->stream));
-    TRY(fetch_sum(ctx, v));
-    *rms = std::sqrt(v[0] / (double)ctx->n3);
-    *mean_t = v[1] / (double)ctx->n3;
+    TRY(fold_step(ctx, ST_M));
+    HIPCHK(source_pass(ctx->phi, ctx->M, step_scal(ctx, ST_M), ctx->cfg.xi_m, ctx->cfg.v_m, ctx->t, ctx->n, ctx->part,
+                       ctx->stream));
+    return fold_step(ctx, ST_SIG2, read);
+}
+
+// rho_bar = mean(M) and rms(Sigma) from the step scalars.
+int mass_state(recon_ctx *ctx, const double *v, double *rho_bar, double *rms)
+{
+    if (ctx->part_pos && v[ST_LOST] != 0.0)
+        return fail(ctx, RECON_E_NO_CONVERGENCE, "%.0f particles not located on the deformed mesh", v[ST_LOST]);
+    *rho_bar = v[ST_M] / (double)ctx->n3;
+    *rms = std::sqrt(v[ST_SIG2] / (double)ctx->n3);
     return RECON_OK;
 }
 
@@ -883,29 +984,35 @@ int forward(recon_ctx *ctx, double box, double tol, double *phi_out, double *del
     const MassTensor K = full ? ctx->Kf : MassTensor{ctx->t, ctx->b, ctx->r, ctx->z, ctx->p, ctx->q, nullptr};
     int it = 0;
     for (; it < c.max_outer; ++it) {
-        double rho_bar, rms, mean_t;
-        TRY(mass_state(ctx, &rho_bar, &rms, &mean_t, !carry || it == 0));
-        st->rms_sigma[it] = rms;
-        st->kappa[it] = rho_bar;
-        if (!std::isfinite(rms)) return fail(ctx, RECON_E_NO_CONVERGENCE, "non-finite mass deviation");
-        if (rms <= c.outer_tol) break;
-        HIPCHK(smooth_pass(ctx->t, ctx->b, ctx->n, c.smooth_center, mean_t, ctx->stream));
+        double rho_bar, rms, v[ST_COUNT];
+        const bool warm = c.warm_start && it > 0;
+        TRY(queue_mass_state(ctx, !carry || it == 0));
+        HIPCHK(smooth_pass(ctx->t, ctx->b, ctx->n, c.smooth_center, step_scal(ctx, ST_T), ctx->stream));
         // the exact-Jacobian solve preconditions with the x ~ xi V-cycle of
         // the mean diagonal of K = M e^-1
         if (full) HIPCHK(launch_mass_tensor(ctx->phi, ctx->M, K, ctx->n, ctx->stream));
         TRY(build_hierarchy(ctx, full ? K.tr : ctx->M));
-        int cyc = 0;
-        double rel = 0.0;
-        TRY(mg_solve(ctx, ctx->M, ctx->b, tol, &cyc, &rel, c.warm_start && it > 0, full ? &K : nullptr));
+        TRY(mg_start(ctx, ctx->M, ctx->b, warm, full ? &K : nullptr));
+        TRY(mg_wait(ctx, v));
+        TRY(mass_state(ctx, v, &rho_bar, &rms));
+        st->rms_sigma[it] = rms;
+        st->kappa[it] = rho_bar;
+        if (!std::isfinite(rms)) return fail(ctx, RECON_E_NO_CONVERGENCE, "non-finite mass deviation");
+        if (rms <= c.outer_tol) break;
+        int cyc = 0, status = RECON_OK;
+        TRY(mg_run(ctx, ctx->M, ctx->b, tol, v, &cyc, &status, warm, full ? &K : nullptr));
+        if (status != RECON_OK) return mg_failed(ctx, tol, cyc);
         st->vcycles[it] = cyc;
         st->vcycles_total += cyc;
-        st->rel_residual[it] = rel;
-        HIPCHK(smooth_pass(ctx->u, ctx->dphi, ctx->n, c.smooth_center, 0.0, ctx->stream));
+        HIPCHK(smooth_pass(ctx->u, ctx->dphi, ctx->n, c.smooth_center, nullptr, ctx->stream));
         if (carry && full) HIPCHK(launch_full_apply(K, ctx->dphi, D, ctx->n, ctx->stream));
         else if (carry) HIPCHK(launch_mass_change(ctx->phi, ctx->M, ctx->dphi, K, D, ctx->n, ctx->stream));
         double alpha = 0.0;
-        TRY(choose_step(ctx, ctx->phi, ctx->dphi, &alpha, carry ? ctx->M : nullptr, carry ? D : nullptr,
-                        &st->alpha_limit[it]));
+        const int rc = choose_step(ctx, ctx->phi, ctx->dphi, &alpha, carry ? ctx->M : nullptr, carry ? D : nullptr,
+                                   &st->alpha_limit[it], v);
+        const double rel = mg_relative(v);
+        st->rel_residual[it] = rel;
+        TRY(rc);
         if (carry) HIPCHK(launch_axpy(ctx->M, D, alpha, n3, ctx->stream));
         HIPCHK(launch_axpy(ctx->phi, ctx->dphi, alpha, n3, ctx->stream));
         st->alpha[it] = alpha;
@@ -921,8 +1028,11 @@ int forward(recon_ctx *ctx, double box, double tol, double *phi_out, double *del
         }
     }
     if (it == c.max_outer) {
-        double rho_bar, rms, mean_t;
-        TRY(mass_state(ctx, &rho_bar, &rms, &mean_t, !carry));
+        double rho_bar, rms, v[ST_COUNT];
+        TRY(queue_mass_state(ctx, !carry, true));
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        read_step(ctx, v);
+        TRY(mass_state(ctx, v, &rho_bar, &rms));
         st->rms_sigma[it] = rms;
         st->kappa[it] = rho_bar;
     }
@@ -961,7 +1071,7 @@ int backward(recon_ctx *ctx, const double *gd, const double *gp, double *grad, c
     double *hb = wsp<double>(ctx, ctx->lo.adj[4]);
     double *xb = wsp<double>(ctx, ctx->lo.adj[5]);
     double *ubar = ctx->b, *tbar = ctx->t;
-    double v[2];
+    double v[ST_COUNT];
     // u_q of the tape as FP64; an FP32 tape is widened into z, which is idle
     // whenever this is called (before a step's solve and right after it)
     auto tape_u = [&](int q) -> const double * {
@@ -981,7 +1091,7 @@ int backward(recon_ctx *ctx, const double *gd, const double *gp, double *grad, c
         for (int q = 0; q < s; ++q) {
             const double *u_q = tape_u(q);
             if (!u_q) return fail(ctx, RECON_E_HIP, "tape widening launch failed");
-            HIPCHK(smooth_pass(u_q, ctx->dphi, n, c.smooth_center, 0.0, ctx->stream));
+            HIPCHK(smooth_pass(u_q, ctx->dphi, n, c.smooth_center, nullptr, ctx->stream));
             HIPCHK(launch_axpy(phi, ctx->dphi, ctx->tape_alpha[q], n3, ctx->stream));
         }
         if (gpos) {
@@ -989,40 +1099,41 @@ int backward(recon_ctx *ctx, const double *gd, const double *gp, double *grad, c
             // step's (ctx->xi holds those of the final mesh after the forward)
             HIPCHK(launch_invert_map(phi, pos, np, n, ctx->box, ctx->xi, ctx->shifts, kInvertIters,
                                      kInvertTol, ctx->part, ctx->stream));
-            TRY(fetch_sum(ctx, v));
-            if (v[0] != 0.0)
-                return fail(ctx, RECON_E_NO_CONVERGENCE, "%.0f particles not located on the mesh of step %d", v[0], s);
+            TRY(fold_step(ctx, ST_LOST));
             HIPCHK(launch_deposit_xi(ctx->xi, np, n, ctx->M, ctx->stream));
             HIPCHK(launch_sum(ctx->M, n3, ctx->part, ctx->stream));
         } else {
             HIPCHK(meshmass_pass(phi, ctx->m, ctx->M, n, ctx->part, ctx->stream));
         }
-        TRY(fetch_sum(ctx, v));
-        const double rho_bar = v[0] / (double)n3;
+        TRY(fold_step(ctx, ST_M));
         // phi_{s+1} = phi_s + alpha S u:  ubar = alpha S phibar, made mean-free
         HIPCHK(launch_smooth_scaled(phibar, ubar, n, c.smooth_center, ctx->tape_alpha[s], ctx->stream));
         HIPCHK(launch_sum(ubar, n3, ctx->part, ctx->stream));
-        TRY(fetch_sum(ctx, v));
-        HIPCHK(launch_fill(ctx->scal + 16, 1, v[0] / (double)n3, ctx->stream));
-        HIPCHK(launch_add_scalar(ubar, ctx->scal + 16, -1.0, 1.0, n3, ctx->stream));
+        TRY(fold_step(ctx, ST_U));
+        HIPCHK(launch_add_mean(ubar, step_scal(ctx, ST_U), -1.0, n3, ctx->stream));
         // u = A(M)^+ b:  lambda = A^+ ubar (same symmetric operator and solver)
         TRY(build_hierarchy(ctx, ctx->M));
-        int cyc = 0;
-        double rel = 0.0;
-        TRY(mg_solve(ctx, ctx->M, ubar, ctx->last_tol, &cyc, &rel));
+        TRY(mg_start(ctx, ctx->M, ubar));
+        TRY(mg_wait(ctx, v));
+        if (gpos && v[ST_LOST] != 0.0)
+            return fail(ctx, RECON_E_NO_CONVERGENCE, "%.0f particles not located on the mesh of step %d", v[ST_LOST],
+                        s);
+        int cyc = 0, status = RECON_OK;
+        TRY(mg_run(ctx, ctx->M, ubar, ctx->last_tol, v, &cyc, &status));
+        if (status != RECON_OK) return mg_failed(ctx, ctx->last_tol, cyc);
         const double *lam = ctx->u;
         const double *u_s = tape_u(s);
         if (!u_s) return fail(ctx, RECON_E_HIP, "tape widening launch failed");
         HIPCHK(launch_coefgrad(lam, u_s, ctx->M, c.a_min, Mbar, n, ctx->stream));
         // b = S t - mean:  tbar = S (lambda - mean lambda)
         HIPCHK(launch_sum(lam, n3, ctx->part, ctx->stream));
-        TRY(fetch_sum(ctx, v));
-        HIPCHK(smooth_pass(lam, tbar, n, c.smooth_center, v[0] / (double)n3, ctx->stream));
+        TRY(fold_step(ctx, ST_U));
+        HIPCHK(smooth_pass(lam, tbar, n, c.smooth_center, step_scal(ctx, ST_U), ctx->stream));
         // source, then Sigma = mean(M) - M
-        HIPCHK(launch_source_adj(phi, ctx->M, rho_bar, tbar, c.xi_m, c.v_m, Mbar, hb, n, ctx->part, ctx->stream));
-        TRY(fetch_sum(ctx, v));
-        HIPCHK(launch_fill(ctx->scal + 16, 1, v[0] / (double)n3, ctx->stream));
-        HIPCHK(launch_add_scalar(Mbar, ctx->scal + 16, 1.0, 1.0, n3, ctx->stream));
+        HIPCHK(launch_source_adj(phi, ctx->M, step_scal(ctx, ST_M), tbar, c.xi_m, c.v_m, Mbar, hb, n, ctx->part,
+                                 ctx->stream));
+        TRY(fold_step(ctx, ST_U));
+        HIPCHK(launch_add_mean(Mbar, step_scal(ctx, ST_U), 1.0, n3, ctx->stream));
         if (gpos) {
             // M = CIC(xi), xi = X^-1(y; D_c phi): xb <- adjoint of the node
             // shifts (still those of this step's phi, from the inversion)
@@ -1440,16 +1551,16 @@ int recon_stage_source(recon_ctx *ctx, const double *phi, const double *M, doubl
     TRY(check_ctx(ctx));
     if (!phi || !M || !b) return fail(ctx, RECON_E_ARG, "null array");
     TRY(outer_variant_ok(ctx, variant));
-    double v[2];
+    double v[ST_COUNT];
     HIPCHK(launch_sum(M, ctx->n3, ctx->part, ctx->stream));
-    TRY(fetch_sum(ctx, v));
-    const double rho_bar = v[0] / (double)ctx->n3;
-    HIPCHK(source_pass(phi, M, rho_bar, ctx->cfg.xi_m, ctx->cfg.v_m, ctx->t, ctx->n, ctx->part, ctx->stream,
-                       variant));
-    TRY(fetch_sum(ctx, v));
-    if (rms_sigma) *rms_sigma = std::sqrt(v[0] / (double)ctx->n3);
-    HIPCHK(smooth_pass(ctx->t, b, ctx->n, ctx->cfg.smooth_center, v[1] / (double)ctx->n3, ctx->stream, variant));
+    TRY(fold_step(ctx, ST_M));
+    HIPCHK(source_pass(phi, M, step_scal(ctx, ST_M), ctx->cfg.xi_m, ctx->cfg.v_m, ctx->t, ctx->n, ctx->part,
+                       ctx->stream, variant));
+    TRY(fold_step(ctx, ST_SIG2, true));
+    HIPCHK(smooth_pass(ctx->t, b, ctx->n, ctx->cfg.smooth_center, step_scal(ctx, ST_T), ctx->stream, variant));
     HIPCHK(hipStreamSynchronize(ctx->stream));
+    read_step(ctx, v);
+    if (rms_sigma) *rms_sigma = std::sqrt(v[ST_SIG2] / (double)ctx->n3);
     return RECON_OK;
 }
 
@@ -1459,7 +1570,7 @@ int recon_stage_smooth(recon_ctx *ctx, const double *f, double *out, int variant
     if (!f || !out) return fail(ctx, RECON_E_ARG, "null array");
     if (overlap(out, ctx->n3 * 8, f, ctx->n3 * 8)) return fail(ctx, RECON_E_ARG, "out overlaps f");
     TRY(outer_variant_ok(ctx, variant));
-    HIPCHK(smooth_pass(f, out, ctx->n, ctx->cfg.smooth_center, 0.0, ctx->stream, variant));
+    HIPCHK(smooth_pass(f, out, ctx->n, ctx->cfg.smooth_center, nullptr, ctx->stream, variant));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     return RECON_OK;
 }
@@ -1820,7 +1931,7 @@ int recon_stage_mg_solve_full(recon_ctx *ctx, const double *a, const double *phi
     HIPCHK(launch_copy(ctx->M, a, ctx->n3, ctx->stream));
     HIPCHK(launch_mass_tensor(phi, ctx->M, ctx->Kf, ctx->n, ctx->stream));
     TRY(build_hierarchy(ctx, ctx->Kf.tr));
-    TRY(mg_solve(ctx, ctx->Kf.tr, b, tol, cycles, rel_residual, false, &ctx->Kf));
+    TRY(mg_solve(ctx, ctx->Kf.tr, b, tol, cycles, rel_residual, &ctx->Kf));
     HIPCHK(launch_copy(u, ctx->u, ctx->n3, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     return RECON_OK;

@@ -225,9 +225,10 @@ hipError_t launch_meshmass(const double *phi, const double *m, double *M, int n,
 
 // t = Sigma + C + E with Sigma = rho_bar - M, C = 4 max(0, xi_m/lambda_0 - 1)^2,
 // E = -2 [sqrt g > v_m] |Sigma|  (App. A, Eq. elliptic and the limiters).
-__global__ void k_source(const double *__restrict__ phi, const double *__restrict__ M, double rho_bar, double xi_m,
-                         double v_m, double *__restrict__ t, int n, int ipb, double *part)
+__global__ void k_source(const double *__restrict__ phi, const double *__restrict__ M, const double *__restrict__ sum_M,
+                         double n3, double xi_m, double v_m, double *__restrict__ t, int n, int ipb, double *part)
 {
+    const double rho_bar = *sum_M / n3;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y * blockDim.y + threadIdx.y;
     double v[2] = {0.0, 0.0};
@@ -251,11 +252,11 @@ __global__ void k_source(const double *__restrict__ phi, const double *__restric
     block_reduce_store<2, RED_SUM>(v, part, block_row());
 }
 
-hipError_t launch_source(const double *phi, const double *M, double rho_bar, double xi_m, double v_m, double *t, int n,
-                         Part &p, hipStream_t s)
+hipError_t launch_source(const double *phi, const double *M, const double *sum_M, double xi_m, double v_m, double *t,
+                         int n, Part &p, hipStream_t s)
 {
     Shape3 sh = shape3(n);
-    k_source<<<sh.grid, sh.block, 0, s>>>(phi, M, rho_bar, xi_m, v_m, t, n, sh.ipb, p.part);
+    k_source<<<sh.grid, sh.block, 0, s>>>(phi, M, sum_M, (double)((long)n * n * n), xi_m, v_m, t, n, sh.ipb, p.part);
     p.blocks = rows_of(sh);
     p.k = 2;
     return hipGetLastError();
@@ -264,8 +265,9 @@ hipError_t launch_source(const double *phi, const double *M, double rho_bar, dou
 // S f = c0 f + (1 - c0)/6 * (six nearest neighbours), minus a constant (the
 // mean, so that the smoothed source is mean-free).
 __global__ void k_smooth(const double *__restrict__ f, double *__restrict__ out, int n, int ipb, double c0, double cn,
-                         double sv)
+                         const double *__restrict__ sum, double n3)
 {
+    const double sv = sum ? *sum / n3 : 0.0;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y * blockDim.y + threadIdx.y;
     if (k >= n || j >= n) return;
@@ -279,10 +281,10 @@ __global__ void k_smooth(const double *__restrict__ f, double *__restrict__ out,
     }
 }
 
-hipError_t launch_smooth(const double *f, double *out, int n, double c0, double sub, hipStream_t s)
+hipError_t launch_smooth(const double *f, double *out, int n, double c0, const double *sum, hipStream_t s)
 {
     Shape3 sh = shape3(n);
-    k_smooth<<<sh.grid, sh.block, 0, s>>>(f, out, n, sh.ipb, c0, (1.0 - c0) / 6.0, sub);
+    k_smooth<<<sh.grid, sh.block, 0, s>>>(f, out, n, sh.ipb, c0, (1.0 - c0) / 6.0, sum, (double)((long)n * n * n));
     return hipGetLastError();
 }
 
@@ -399,16 +401,16 @@ hipError_t launch_axpy(double *y, const X *x, double alpha, long n3, hipStream_t
 template hipError_t launch_axpy<double>(double *, const double *, double, long, hipStream_t, const double *);
 template hipError_t launch_axpy<float>(double *, const float *, double, long, hipStream_t, const double *);
 
-// y += sign * (*c) * scale
-__global__ void k_add_scalar(double *__restrict__ y, const double *c, double sign, double scale, long n3)
+// y += sign * mean, the mean of a field whose sum over n3 nodes is *sum
+__global__ void k_add_mean(double *__restrict__ y, const double *__restrict__ sum, double sign, long n3)
 {
-    const double v = sign * (*c) * scale;
+    const double v = sign * (*sum / (double)n3);
     for (long p = blockIdx.x * 256L + threadIdx.x; p < n3; p += 256L * gridDim.x) y[p] += v;
 }
 
-hipError_t launch_add_scalar(double *y, const double *c_dev, double sign, double scale, long n3, hipStream_t s)
+hipError_t launch_add_mean(double *y, const double *sum, double sign, long n3, hipStream_t s)
 {
-    k_add_scalar<<<flat_blocks(n3), 256, 0, s>>>(y, c_dev, sign, scale, n3);
+    k_add_mean<<<flat_blocks(n3), 256, 0, s>>>(y, sum, sign, n3);
     return hipGetLastError();
 }
 

@@ -521,10 +521,34 @@ __global__ void __launch_bounds__(NT_, MINW) k_rbgs_fused(const T *__restrict__ 
 template <typename T, int TJ_, int TK_, int NT_, int MINW_, int SLOTS_, int FOLD_ = 1, int CI_ = 0>
 struct FusedShape {
     static constexpr int TJ = TJ_, TK = TK_, NT = NT_, MINW = MINW_, SLOTS = SLOTS_, MIN_BLOCKS = 512;
+    // workgroups that a CU holds: two 50-76 KB rings, or one
+    static constexpr int PER_CU = SLOTS_ * (TJ_ + 4) * (TK_ + 4) * 2 * (int)sizeof(T) <= 80 * 1024 ? 2 : 1;
     static constexpr bool FOLD = FOLD_;
     static constexpr int CI = CI_;
     static constexpr int NTS = CI_ == 0;  // the streaming shapes store nontemporally
 };
+
+// i-planes per workgroup of a streaming shape.  The longest chunk that keeps
+// MIN_BLOCKS workgroups, unless another divisor of the edge takes clearly
+// fewer plane steps: the rounds of workgroups on 256 CUs times the chunk and
+// the four planes that it reads again.  Whole solves: FP64 320^3 241 -> 221 ms
+// (500 workgroups of 64 planes in two rounds instead of 800 of 40 in four),
+// 384^3 423 -> 406, 256^3 113.5 -> 110.3 (one round of 256 workgroups); FP32
+// 384^3 284 -> 262.  512^3 keeps its first choice.
+template <typename C>
+int fused_chunk(int n)
+{
+    const int tiles = (n / C::TK) * (n / C::TJ);
+    int ci = n;
+    while (ci > 16 && tiles * (n / ci) < C::MIN_BLOCKS) ci /= 2;
+    auto steps = [&](int c) {
+        const int rounds = (tiles * (n / c) + 256 * C::PER_CU - 1) / (256 * C::PER_CU);
+        return rounds * (c + 4);
+    };
+    for (int c = 16; c <= n; c += 4)
+        if (n % c == 0 && (n % ci || steps(c) * 100 < steps(ci) * 95)) ci = c;
+    return ci;
+}
 
 template <typename C, typename T>
 hipError_t launch_fused_shape(const T *u_in, T *u_out, const T *a, const T *b, int n, T inv, T a_min, int first,
@@ -532,9 +556,7 @@ hipError_t launch_fused_shape(const T *u_in, T *u_out, const T *a, const T *b, i
 {
     if (e && (zero_init || n % 2)) return hipErrorInvalidValue;
     if (n < C::TK || n % C::TK || n % C::TJ) return hipErrorInvalidValue;
-    int ci = C::CI ? C::CI : n;
-    if (!C::CI)
-        while (ci > 16 && (n / C::TK) * (n / C::TJ) * (n / ci) < C::MIN_BLOCKS) ci /= 2;
+    const int ci = C::CI ? C::CI : fused_chunk<C>(n);
     if (n % ci || (C::SLOTS == 4 && ci % 4)) return hipErrorInvalidValue;  // the 4-slot loop takes planes in fours
     const int nblk = (n / C::TK) * (n / C::TJ) * (n / ci);
 #define RECON_FUSED(Z, F1)                                                                                \
@@ -562,12 +584,15 @@ hipError_t launch_fused_shape(const T *u_in, T *u_out, const T *a, const T *b, i
     return hipGetLastError();
 }
 
-// The shapes of levels from 256^3 whose edge they divide.
+// The shapes of levels from 256^3 whose edge they divide: FP32 takes 16 x 64
+// tiles on edges that are odd multiples of 64 (320^3 solves 186 ms with the
+// narrow tiles below, 167 with 8 x 64, 165 with 16 x 64; at 192^3 the narrow
+// tiles are as good in FP32 and 4% better in FP64).
 template <typename T>
 bool fused_large(int n)
 {
-    const int tk = sizeof(T) == 4 ? 128 : 64, tj = sizeof(T) == 4 ? (n >= 1024 ? 16 : 8) : 16;
-    return n >= 256 && n % tk == 0 && n % tj == 0;
+    const int tj = sizeof(T) == 4 && n >= 1024 && n % 128 == 0 ? 16 : 8;
+    return n >= 256 && n % 64 == 0 && n % (sizeof(T) == 4 && n % 128 == 0 ? tj : 16) == 0;
 }
 
 // Every shape divides the edges it is used for: the large ones above, the
@@ -599,6 +624,9 @@ hipError_t launch_rbgs_fused(const T *u_in, T *u_out, const T *a, const T *b, in
                                                                         zero_init, s, e);
     }
     if constexpr (sizeof(T) == 4) {
+        if (n % 128)
+            return launch_fused_shape<FusedShape<T, 16, 64, 512, 2, 4>>(u_in, u_out, a, b, n, inv, a_min, first,
+                                                                       zero_init, s, e);
         if (n >= 1024 && !zero_init)
             return launch_fused_shape<FusedShape<T, 16, 128, 512, 1, 6>>(u_in, u_out, a, b, n, inv, a_min, first,
                                                                         zero_init, s, e);

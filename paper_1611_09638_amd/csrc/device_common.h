@@ -33,8 +33,46 @@ __device__ __forceinline__ double red_identity()
     return INFINITY;
 }
 
+template <int OFF>
+__device__ __forceinline__ double lane_down(double v)  // lane i gets lane i + OFF of its 16
+{
+    union {
+        double d;
+        int w[2];
+    } x;
+    x.d = v;
+    x.w[0] = __builtin_amdgcn_update_dpp(0, x.w[0], 0x100 | OFF, 15, 15, true);
+    x.w[1] = __builtin_amdgcn_update_dpp(0, x.w[1], 0x100 | OFF, 15, 15, true);
+    return x.d;
+}
+
+// Reduction over a 64-lane wave by halving (lane i takes lane i + 32, then 16,
+// 8, 4, 2, 1): lane 0 gets the result, the others nothing of use.  In registers
+// (half-wave swaps, then row shifts): a shuffle through LDS per step was most
+// of a small reducing kernel's time.
+template <int OP>
+__device__ __forceinline__ double wave_reduce(double x)
+{
+    union {
+        double d;
+        unsigned w[2];
+    } a, b;
+    a.d = x;
+    b.w[0] = __builtin_amdgcn_permlane32_swap(a.w[0], a.w[0], false, false)[1];
+    b.w[1] = __builtin_amdgcn_permlane32_swap(a.w[1], a.w[1], false, false)[1];
+    x = red_op<OP>(x, b.d);
+    a.d = x;
+    b.w[0] = __builtin_amdgcn_permlane16_swap(a.w[0], a.w[0], false, false)[1];
+    b.w[1] = __builtin_amdgcn_permlane16_swap(a.w[1], a.w[1], false, false)[1];
+    x = red_op<OP>(x, b.d);
+    x = red_op<OP>(x, lane_down<8>(x));
+    x = red_op<OP>(x, lane_down<4>(x));
+    x = red_op<OP>(x, lane_down<2>(x));
+    return red_op<OP>(x, lane_down<1>(x));
+}
+
 // Block reduction of K values per thread into one row of partials.  Fixed
-// order: wavefront butterfly (64 lanes), then waves in index order.
+// order: halving within a wavefront (64 lanes), then waves in index order.
 // Blocks must have at most 256 threads; blocks that are not a whole number of
 // 64-lane waves (grids below 8^3) take an LDS tree instead of the shuffles.
 template <int K, int OP>
@@ -62,11 +100,7 @@ __device__ void block_reduce_store(double (&v)[K], double *part, int row)
     }
     const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-    for (int c = 0; c < K; ++c) {
-        double x = v[c];
-        for (int off = 32; off > 0; off >>= 1) x = red_op<OP>(x, __shfl_down(x, off, 64));
-        v[c] = x;
-    }
+    for (int c = 0; c < K; ++c) v[c] = wave_reduce<OP>(v[c]);
     if (lane == 0) {
 #pragma unroll
         for (int c = 0; c < K; ++c) sm[wave][c] = v[c];
@@ -81,19 +115,6 @@ __device__ void block_reduce_store(double (&v)[K], double *part, int row)
             part[(size_t)row * K + c] = x;
         }
     }
-}
-
-template <int OFF>
-__device__ __forceinline__ double lane_down(double v)  // lane i gets lane i + OFF of its 16
-{
-    union {
-        double d;
-        int w[2];
-    } x;
-    x.d = v;
-    x.w[0] = __builtin_amdgcn_update_dpp(0, x.w[0], 0x100 | OFF, 15, 15, true);
-    x.w[1] = __builtin_amdgcn_update_dpp(0, x.w[1], 0x100 | OFF, 15, 15, true);
-    return x.d;
 }
 
 // The sums of `rows` rows of K partials in the order of reduce_finalize (thread

@@ -231,6 +231,13 @@ hipError_t launch_update_pq(const Z *z, const double *a, double *pv, double *q, 
 template <typename Z>
 hipError_t launch_direction(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
                             double a_min, bool first, double *ks, const Part &dots, Part &p, hipStream_t s);
+// The same streamed through LDS (stencil25.hip), with z.r and z.q in ks, and
+// with u (not first) also u += ks[KS_ALPHA] p_old; edges that are multiples of
+// 64 from 128.  The partials are the gather's, so the sum is.
+bool direction_grouped_supported(int n);
+template <typename Z>
+hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
+                                    double a_min, bool first, double *u, const double *ks, Part &p, hipStream_t s);
 // u += alpha p (if u != null); r -= alpha q; partial K=1: sum r^2; r32 = (float) r if r32 != null.
 // With ks != null: alpha = ks[KS_RZ] / ks[KS_PQ], and the kernel stores it in
 // ks[KS_ALPHA] and ks[KS_RZ] in ks[KS_RZ_OLD].  pq with blocks > 0: the K=1

@@ -444,15 +444,17 @@ hipError_t restrict_level(const T *f, T *c, int n, hipStream_t s, int variant = 
     return launch_restrict<T>(f, c, n, s);
 }
 
-// Coarse right-hand side c = R (b - scale A u): streaming levels whose coarse
-// edge is a multiple of 32 form it in one fused pass; otherwise the residual
-// goes through `res` (a fine-level buffer) and is then restricted.  variant:
-// 0 = that choice, 1 = the two passes, 2 = the fused pass.
+// Coarse right-hand side c = R (b - scale A u): levels from 128^3 whose coarse
+// edge is a multiple of 32 form it in one fused pass (against the two passes,
+// whole solves: 320^3 257 -> 241 ms in FP64, 192^3 49.1 -> 47.6 in FP32, 128^3
+// 1.5% in both); otherwise the residual goes through `res` (a fine-level
+// buffer) and is then restricted.  variant: 0 = that choice, 1 = the two
+// passes, 2 = the fused pass.
 template <typename T>
 hipError_t coarse_rhs(const T *u, const T *a, const T *b, T *res, T *c, int n, T scale, T a_min, hipStream_t s,
                       int variant = 0)
 {
-    if (variant == 2 || (variant == 0 && use_stream<T>(n) && resrestrict25_supported<T>(n)))
+    if (variant == 2 || (variant == 0 && n >= 128 && resrestrict25_supported<T>(n)))
         return launch_resrestrict25<T>(u, a, b, c, n, scale, a_min, s);
     hipError_t e = residual_level<T>(u, a, b, res, n, scale, a_min, s);
     if (e != hipSuccess) return e;
@@ -717,13 +719,6 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
         cycles = 1;
         if (mixed) HIPCHK(launch_dots_zr_zq<float>(ctx->L32.u[0], ctx->r, nullptr, n3, ctx->part, ctx->stream));
         else HIPCHK(launch_dots_zr_zq<double>(ctx->z, ctx->r, nullptr, n3, ctx->part, ctx->stream));
-        // Small grids: the direction and the residual update fold the partials
-        // of the sums they need themselves (dots and pq, in separate halves of
-        // the partials), and the direction is one gather launch.
-        const bool small = !Kf && fold_in_consumer(n);
-        Part dots = ctx->part, pq = ctx->part;
-        pq.part = ctx->part.part + kPartCap / 2;
-        if (!small) HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
         bool first = true;
         // Streaming levels form the new direction out of place, fused with its
         // operator product; it alternates between p and t (idle during a solve),
@@ -731,6 +726,19 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
         // u += alpha p of one step is deferred into the next direction pass there
         // (it reads p anyway), and applied after the loop for the last step.
         const bool stream = use_stream<double>(n) && (!Kf || full25_supported(n));
+        // Small grids: the direction and the residual update fold the partials
+        // of the sums they need themselves (dots and pq, in separate halves of
+        // the partials), and the direction is one gather launch.
+        const bool fold = !Kf && fold_in_consumer(n);
+        // Above, edges that are multiples of 64 stream it, with the partials that
+        // the gather launches leave.
+        const bool grouped = !Kf && !stream && !fold && direction_grouped_supported(n);
+        Part dots = ctx->part, pq = ctx->part;
+        pq.part = ctx->part.part + kPartCap / 2;
+        if (!fold) {
+            HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
+            dots.blocks = 0;
+        }
         double *pc = ctx->p, *pn = ctx->t;
         auto f32 = [](double *x) { return reinterpret_cast<float *>(x); };
         bool due = false;
@@ -761,13 +769,23 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
                 if (mixed) HIPCHK(launch_update_p<float>(ctx->L32.u[0], pc, 0.0, n3, first, ks, ctx->stream));
                 else HIPCHK(launch_update_p<double>(ctx->z, pc, 0.0, n3, first, ks, ctx->stream));
                 HIPCHK(launch_full_apply_dot(*Kf, pc, ctx->q, n, ctx->cfg.a_min, ctx->part, ctx->stream));
-            } else if (small) {
+            } else if (fold) {
                 if (mixed)
                     HIPCHK(launch_direction<float>(ctx->L32.u[0], pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first, ks, dots,
                                                    pq, ctx->stream));
                 else
                     HIPCHK(launch_direction<double>(ctx->z, pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first, ks, dots, pq,
                                                     ctx->stream));
+                std::swap(pc, pn);
+            } else if (grouped) {
+                double *ud = due ? ctx->u : nullptr;
+                if (mixed)
+                    HIPCHK(launch_direction_grouped<float>(ctx->L32.u[0], pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first,
+                                                           ud, ks, pq, ctx->stream));
+                else
+                    HIPCHK(launch_direction_grouped<double>(ctx->z, pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first, ud,
+                                                            ks, pq, ctx->stream));
+                due = false;
                 std::swap(pc, pn);
             } else if (mixed) {
                 HIPCHK(launch_update_pq<float>(ctx->L32.u[0], a0, pc, ctx->q, 0.0, n, ctx->cfg.a_min, first, ks,
@@ -777,10 +795,10 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
                                                 ctx->stream));
             }
             first = false;
-            if (!small) HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_PQ, ctx->stream));
-            HIPCHK(launch_update_ur(stream ? nullptr : ctx->u, ctx->r, pc, ctx->q, 0.0, r32, n3, ks, ctx->part,
-                                    ctx->stream, small ? &pq : nullptr));
-            due = stream;
+            if (!fold) HIPCHK(reduce_finalize(grouped ? pq : ctx->part, sums, ks + KS_PQ, ctx->stream));
+            due = stream || grouped;
+            HIPCHK(launch_update_ur(due ? nullptr : ctx->u, ctx->r, pc, ctx->q, 0.0, r32, n3, ks, ctx->part,
+                                    ctx->stream, fold ? &pq : nullptr));
             // The stop test needs ||r|| on the host.  When this step cannot be
             // the last (a fixed count not yet reached, or the residual norm
             // extrapolated from the last two steps still well above the
@@ -807,10 +825,10 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
             ++cycles;
             if (mixed) HIPCHK(launch_dots_zr_zq<float>(ctx->L32.u[0], ctx->r, ctx->q, n3, ctx->part, ctx->stream));
             else HIPCHK(launch_dots_zr_zq<double>(ctx->z, ctx->r, ctx->q, n3, ctx->part, ctx->stream));
-            dots = ctx->part;
-            if (!small) HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
+            if (fold) dots = ctx->part;
+            else HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
         }
-        if (due && mixed) HIPCHK(launch_axpy(ctx->u, f32(pc), 0.0, n3, ctx->stream, ks + KS_ALPHA));
+        if (due && mixed && stream) HIPCHK(launch_axpy(ctx->u, f32(pc), 0.0, n3, ctx->stream, ks + KS_ALPHA));
         else if (due) HIPCHK(launch_axpy(ctx->u, pc, 0.0, n3, ctx->stream, ks + KS_ALPHA));
     }
     // mean-free solution, then the true residual

@@ -20,39 +20,64 @@ struct OpsK {
     int op[8];
 };
 
-// With host != null the launch also copies `count` doubles from `from` to host
-// memory that the device can write.
-__global__ void k_finalize(const double *__restrict__ part, int rows, int K, OpsK ops, double *out, const double *from,
-                           double *host, int count)
+// Thread t of 256 folds rows t, t + 256, ... in order (sixteen rows' loads in
+// flight), a halving tree folds the threads.  With host != null the launch
+// also copies `count` doubles from `from` to host memory that the device can
+// write.
+template <int K>
+__global__ void __launch_bounds__(256) k_finalize(const double *__restrict__ part, int rows, OpsK ops, double *out,
+                                                  const double *from, double *host, int count)
 {
-    __shared__ double sm[256];
+    __shared__ double sm[K][256];
     const int t = threadIdx.x;
-    for (int c = 0; c < K; ++c) {
-        const int op = ops.op[c];
-        auto fold = [op](double x, double y) {
-            return op == RED_SUM ? x + y : (op == RED_MAX ? (x > y ? x : y) : (x < y ? x : y));
-        };
-        double x = op == RED_SUM ? 0.0 : (op == RED_MAX ? -INFINITY : INFINITY);
-        // rows t, t + 256, ... in order; eight loads in flight at a time
-        int r = t;
-        for (; r + 7 * 256 < rows; r += 8 * 256) {
-            double y[8];
+    auto fold = [](int op, double x, double y) {
+        return op == RED_SUM ? x + y : (op == RED_MAX ? (x > y ? x : y) : (x < y ? x : y));
+    };
+    double x[K];
 #pragma unroll
-            for (int v = 0; v < 8; ++v) y[v] = part[(size_t)(r + v * 256) * K + c];
+    for (int c = 0; c < K; ++c) x[c] = ops.op[c] == RED_SUM ? 0.0 : (ops.op[c] == RED_MAX ? -INFINITY : INFINITY);
+    constexpr int UN = 16;
+    int r = t;
+    for (; r + (UN - 1) * 256 < rows; r += UN * 256) {
+        double y[UN][K];
 #pragma unroll
-            for (int v = 0; v < 8; ++v) x = fold(x, y[v]);
-        }
-        for (; r < rows; r += 256) x = fold(x, part[(size_t)r * K + c]);
-        sm[t] = x;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (t < w) sm[t] = fold(sm[t], sm[t + w]);
-            __syncthreads();
-        }
-        if (t == 0) out[c] = sm[0];
-        __syncthreads();
+        for (int v = 0; v < UN; ++v)
+#pragma unroll
+            for (int c = 0; c < K; ++c) y[v][c] = part[(size_t)(r + v * 256) * K + c];
+#pragma unroll
+        for (int v = 0; v < UN; ++v)
+#pragma unroll
+            for (int c = 0; c < K; ++c) x[c] = fold(ops.op[c], x[c], y[v][c]);
     }
-    if (host && t < count) host[t] = from[t];
+    for (; r < rows; r += 256)
+#pragma unroll
+        for (int c = 0; c < K; ++c) x[c] = fold(ops.op[c], x[c], part[(size_t)r * K + c]);
+#pragma unroll
+    for (int c = 0; c < K; ++c) sm[c][t] = x[c];
+    __syncthreads();
+    if (t < 64) {
+#pragma unroll
+        for (int c = 0; c < K; ++c) {
+            const int op = ops.op[c];
+            double m[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) m[q] = sm[c][(t & 15) + 16 * q];
+#pragma unroll
+            for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+                for (int q = 0; q < h; ++q) m[q] = fold(op, m[q], m[q + h]);
+            double v = m[0];
+            v = fold(op, v, lane_down<8>(v));
+            v = fold(op, v, lane_down<4>(v));
+            v = fold(op, v, lane_down<2>(v));
+            v = fold(op, v, lane_down<1>(v));
+            if (t == 0) out[c] = v;
+        }
+    }
+    if (host) {
+        __syncthreads();
+        if (t < count) host[t] = from[t];
+    }
 }
 
 hipError_t reduce_finalize(const Part &p, const int *ops, double *out, hipStream_t s, const double *from, double *host,
@@ -60,7 +85,13 @@ hipError_t reduce_finalize(const Part &p, const int *ops, double *out, hipStream
 {
     OpsK o;
     for (int c = 0; c < 8; ++c) o.op[c] = c < p.k ? ops[c] : RED_SUM;
-    k_finalize<<<1, 256, 0, s>>>(p.part, p.blocks, p.k, o, out, from, host, count);
+    switch (p.k) {
+    case 1: k_finalize<1><<<1, 256, 0, s>>>(p.part, p.blocks, o, out, from, host, count); break;
+    case 2: k_finalize<2><<<1, 256, 0, s>>>(p.part, p.blocks, o, out, from, host, count); break;
+    case 3: k_finalize<3><<<1, 256, 0, s>>>(p.part, p.blocks, o, out, from, host, count); break;
+    case 4: k_finalize<4><<<1, 256, 0, s>>>(p.part, p.blocks, o, out, from, host, count); break;
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
@@ -864,19 +895,19 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 // r and its FP32 copy are stored nontemporally: the next kernels that read
 // them stream fields far larger than the caches, and keeping the stores out
 // of L2 measured faster at 256^3 and 512^3.
-template <bool U>
-__global__ void k_update_ur(double *__restrict__ u, double *__restrict__ r, const double *__restrict__ pv,
+// FOLD: p.q is still partials (pq, rows), folded by every workgroup.
+template <bool U, bool FOLD>
+__global__ void __launch_bounds__(U ? 256 : 1024) k_update_ur(double *__restrict__ u, double *__restrict__ r, const double *__restrict__ pv,
                             const double *__restrict__ q, double alpha, float *__restrict__ r32, long n3, double *part,
                             double *ks, const double *__restrict__ pq, int rows)
 {
     if (ks) {
         const double rz = ks[KS_RZ];
         double d[1];
-        if (rows > 0) fold_sums<1>(pq, rows, d);
+        if constexpr (FOLD) fold_sums<1>(pq, rows, d);
         else d[0] = ks[KS_PQ];
         alpha = rz / d[0];
-        // only this kernel's other lanes read ks, and only KS_RZ and (without
-        // rows) KS_PQ
+        // only this kernel's other lanes read ks, and only KS_RZ and KS_PQ
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             ks[KS_ALPHA] = alpha;
             ks[KS_RZ_OLD] = rz;
@@ -948,8 +979,11 @@ hipError_t launch_update_ur(double *u, double *r, const double *pv, const double
     // up to 16384 workgroups (measured 755 against 813 us at 512^3 with 8192)
     const long pairs = (n3 + 1) / 2;
     const int nb = (int)std::min<long>((pairs + 255) / 256, 16384);
-    if (u) k_update_ur<true><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, rows ? pq->part : nullptr, rows);
-    else k_update_ur<false><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, rows ? pq->part : nullptr, rows);
+    const double *part = rows ? pq->part : nullptr;
+    if (u && rows) k_update_ur<true, true><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, part, rows);
+    else if (u) k_update_ur<true, false><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, part, rows);
+    else if (rows) k_update_ur<false, true><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, part, rows);
+    else k_update_ur<false, false><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, part, rows);
     p.blocks = nb;
     p.k = 1;
     return hipGetLastError();

@@ -60,14 +60,19 @@ __device__ __forceinline__ void lds_fence_barrier()
 // P (direction only): storage type of p_old and p_new.  With P = float the new
 // direction is rounded to FP32 as it is formed, so the stored p_new is exactly
 // the operand of A and of the later solution update.
+// GRP (directions on 64-wide tiles, where a wave is a row of 64): the partial
+// sums are rows of 64 x 4 nodes and ipb planes, as the gather kernels leave
+// them, so the sums round like theirs (GRP = 2: and plain stores, for grids that
+// stay in the caches); GRP = 0: one partial per workgroup.
 template <typename T, typename Z, int MODE, int TJ, int NT, int TK = 64, int FIRST = 0, int UPD = 0,
-          typename P = T>
+          typename P = T, int GRP = 0>
 __global__ void __launch_bounds__(NT)
     k_flux25(const P *__restrict__ xin, const Z *__restrict__ zg, const T *__restrict__ ag,
              const T *__restrict__ bg, T *__restrict__ out, float *__restrict__ out32, P *__restrict__ pout, int n,
              int ci, T scale, T a_min, T beta, double *part, double *__restrict__ ug, double alpha_u,
-             const double *__restrict__ ks)
+             const double *__restrict__ ks, int ipb = 0)
 {
+    static_assert(!GRP || (MODE == S25_DIRECTION && TK == 64 && TJ % 4 == 0), "a wave is a row of 64 nodes");
     if constexpr (MODE == S25_DIRECTION && !FIRST) {
         // the step sizes of the conjugate-gradient loop, formed on the device
         if (ks) {
@@ -179,6 +184,15 @@ __global__ void __launch_bounds__(NT)
         }
     }
     double v = 0.0;
+    double vg[GRP ? RS : 1];
+    __shared__ double sums[GRP ? TJ : 1];
+    if constexpr (GRP)
+#pragma unroll
+        for (int r = 0; r < RS; ++r) vg[r] = 0.0;
+    auto store = [](auto x, auto *dst) {
+        if constexpr (GRP == 2) *dst = x;
+        else __builtin_nontemporal_store(x, dst);
+    };
 
     auto compute = [&](int p, int set) {
         const int sc = (p - i0) & 1, su = sc ^ 1;
@@ -204,14 +218,33 @@ __global__ void __launch_bounds__(NT)
                 if (out32) __builtin_nontemporal_store((float)rv, &out32[g]);
                 v += rv * rv;
             } else {
-                __builtin_nontemporal_store((P)xc, &pout[g]);
-                __builtin_nontemporal_store(acc, &out[g]);
-                v += xc * acc;
-                if constexpr (UPD) __builtin_nontemporal_store(ru[set][r] + alpha_u * (double)rq[set][r], &ug[g]);
+                store((P)xc, &pout[g]);
+                store(acc, &out[g]);
+                if constexpr (GRP) vg[r] += xc * acc;
+                else v += xc * acc;
+                if constexpr (UPD) store(ru[set][r] + alpha_u * (double)rq[set][r], &ug[g]);
             }
             xd[r] = xc;
             hd[r] = hc;
         }
+        if constexpr (GRP)
+            if ((p + 1) % ipb == 0 || p + 1 == n) {
+#pragma unroll
+                for (int r = 0; r < RS; ++r) {
+                    const double x = wave_reduce<RED_SUM>(vg[r]);
+                    if ((tid & 63) == 0) sums[(tid + r * NT) / 64] = x;
+                    vg[r] = 0.0;
+                }
+            }
+    };
+    // (between the two barriers behind a plane) the rows its last group left
+    auto group = [&](int p) {
+        if constexpr (GRP)
+            if (((p + 1) % ipb == 0 || p + 1 == n) && tid < TJ / 4) {
+                double x = sums[4 * tid];
+                for (int w = 1; w < 4; ++w) x += sums[4 * tid + w];
+                part[tk + (size_t)tiles_k * (j0 / 4 + tid + (size_t)(n / 4) * (p / ipb))] = x;
+            }
     };
 
     // prologue: planes i0 and i0+1 resident, i0+2 and i0+3 staged
@@ -231,12 +264,13 @@ __global__ void __launch_bounds__(NT)
             const int p = s + h;
             compute(p, h);
             lds_fence_barrier();
+            group(p);
             deposit(h, (p - i0) & 1);  // plane p + 2 into the slot of plane p
             lds_fence_barrier();
             fetch(h, p + 4);
         }
     }
-    if constexpr (MODE != S25_RESID) {
+    if constexpr (MODE != S25_RESID && !GRP) {
         double vv[1] = {v};
         block_reduce_store<1, RED_SUM>(vv, part, blockIdx.x);
     }
@@ -325,6 +359,56 @@ hipError_t launch_residual_norm25(const double *u, const double *a, const double
     p.k = 1;
     return hipGetLastError();
 }
+
+// The direction with the gather kernels' rows of partials.  Chunks are even
+// and whole groups of ipb; 6-8 planes below 256^3, where more would leave CUs
+// without a workgroup (128^3: 23.6 ms per solve against 24.1 with 4 planes, 24.4
+// with 16), up to 24 above (320^3: equal from 4 to 80).  Against the two gather
+// launches and p read again by the solution update: 128^3 37 -> 25.6 us, 320^3
+// 623 -> 430 us (its 56 B/node take 300 us at the copy rate).
+static int grouped_chunk(int n)
+{
+    const int ipb = shape3(n).ipb, most = n < 256 ? 8 : 24;
+    int ci = 0;
+    for (int c = 2; c <= n; c += 2)
+        if (n % c == 0 && c % ipb == 0 && (ci == 0 || c <= most)) ci = c;
+    return ci;
+}
+
+bool direction_grouped_supported(int n) { return n >= 128 && n % 64 == 0 && grouped_chunk(n) > 0; }
+
+template <typename Z>
+hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
+                                    double a_min, bool first, double *u, const double *ks, Part &p, hipStream_t s)
+{
+    constexpr int TJ = 16, NT = 512;
+    if (!direction_grouped_supported(n) || p_old == p_new || (u && (first || p_old == u || p_new == u || u == q)))
+        return hipErrorInvalidValue;
+    const int ipb = shape3(n).ipb, ci = grouped_chunk(n), nb = (n / 64) * (n / TJ) * (n / ci);
+    const long rows = (long)(n / 64) * (n / 4) * ((n + ipb - 1) / ipb);
+    if (rows > kPartCap / 2) return hipErrorInvalidValue;
+#define RECON_GRP(FIRST, UPD, G)                                                                                   \
+    k_flux25<double, Z, S25_DIRECTION, TJ, NT, 64, FIRST, UPD, double, G><<<nb, NT, 0, s>>>(                       \
+        p_old, z, a, nullptr, q, nullptr, p_new, n, ci, 1.0, a_min, 0.0, p.part, u, 0.0, ks, ipb)
+    if (n < 256) {
+        if (first) RECON_GRP(1, 0, 2);
+        else if (u) RECON_GRP(0, 1, 2);
+        else RECON_GRP(0, 0, 2);
+    } else {
+        if (first) RECON_GRP(1, 0, 1);
+        else if (u) RECON_GRP(0, 1, 1);
+        else RECON_GRP(0, 0, 1);
+    }
+#undef RECON_GRP
+    p.blocks = (int)rows;
+    p.k = 1;
+    return hipGetLastError();
+}
+template hipError_t launch_direction_grouped<double>(const double *, const double *, double *, const double *,
+                                                     double *, int, double, bool, double *, const double *, Part &,
+                                                     hipStream_t);
+template hipError_t launch_direction_grouped<float>(const float *, const double *, double *, const double *, double *,
+                                                    int, double, bool, double *, const double *, Part &, hipStream_t);
 
 template <typename Z, typename P>
 hipError_t launch_direction25(const Z *z, const P *p_old, P *p_new, const double *a, double *q, double beta, int n,

@@ -99,3 +99,58 @@ def test_krylov_steps_on_small_grids(torch_cuda, n, cn, dtype):
     assert rel(g.cpu().numpy(), u) < 1e-9
     if dtype == 64:
         assert cyc == cycles
+
+
+@pytest.mark.parametrize("n,cn,dtype", [(192, 6, 64), (320, 10, 64), (320, 10, 32), (384, 12, 64), (384, 12, 32)])
+def test_sweeps_on_ragged_edges(torch_cuda, n, cn, dtype):
+    """The fused sweep at the edges whose chunk length or tile is not that of a
+    power of two: every kind (from zero, plain, with the coarse correction)
+    equals the per-colour kernels bit for bit."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    t = torch.float64 if dtype == 64 else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    u, a, b = (torch.randn((n, n, n), generator=gen, device="cuda", dtype=t) for _ in range(3))
+    a = torch.exp(a)
+    e = torch.randn((n // 2,) * 3, generator=gen, device="cuda", dtype=t)
+    rec = binding.Recon(n, binding.Config(coarse_n=cn, precision=binding.MIXED))
+    for first in (0, 1):
+        for x in (u, torch.zeros_like(u)):
+            assert torch.equal(rec.rbgs(x, a, b, first=first, variant=2), rec.rbgs(x, a, b, first=first, variant=1))
+    want = rec.rbgs(rec.prolong_add(u, e, variant=1), a, b, first=1, variant=1)
+    assert torch.equal(rec.prolong_sweep(u, e, a, b, first=1, variant=2), want)
+
+
+@pytest.mark.parametrize("n,cn,mixed", [(128, 8, False), (192, 12, True), (320, 10, False)])
+def test_grouped_direction_sums_like_the_gather(torch_cuda, n, cn, mixed):
+    """The streamed direction of edges that are multiples of 64 leaves the
+    gather kernels' partial sums, so one conjugate-gradient step (one V-cycle,
+    alpha = z.r / p.q) equals the step formed from the stage calls to FP64
+    rounding of the final update alone."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(n + 1)
+    a = torch.exp(torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64))
+    b = torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64)
+    b -= b.mean()
+    cfg = binding.Config(coarse_n=cn, precision=binding.MIXED if mixed else binding.FP64, fixed_cycles=2)
+    rec = binding.Recon(n, cfg)
+    u, cycles, _ = rec.mg_solve(a, b)
+    assert cycles == 2
+    # one V-cycle on the solve's own hierarchy (in mixed mode the FP64 one,
+    # rounded): the plain iteration's first step from zero, less its mean, which
+    # neither the operator nor a product with a mean-free field sees
+    one = binding.Recon(n, binding.Config(coarse_n=cn, precision=cfg.precision, solver=binding.SOLVER_VCYCLE,
+                                          fixed_cycles=1))
+    r, want, p, q, alpha, rz = b.clone(), torch.zeros_like(b), None, None, 0.0, 0.0
+    for step in range(2):
+        z, _, _ = one.mg_solve(a, r)
+        old, rz = rz, float((z * r).sum())
+        beta = 0.0 if step == 0 else -alpha * float((z * q).sum()) / old
+        p, q, pq = rec.direction(z, p, a, beta, first=step == 0, variant=1)
+        alpha = rz / pq
+        want += alpha * p
+        r -= alpha * q
+    want -= want.mean()
+    # the stage steps' sums (torch's) differ from the loop's by about n^1.5 ulp
+    assert float((u - want).norm() / want.norm()) < 1e-11

@@ -22,6 +22,8 @@ enum KrylovScalar {
     KS_RR = 3,      // ||r||^2 after the update
     KS_ALPHA = 4,   // alpha = rz / pq (written by the residual update)
     KS_RZ_OLD = 5,  // rz of the previous step (written by the residual update)
+    KS_ALPHA1 = 6,  // alpha one step before KS_ALPHA
+    KS_ALPHA2 = 7,  // and two steps before
     KS_COUNT = 8
 };
 enum RedOp { RED_SUM = 0, RED_MAX = 1, RED_MIN = 2 };
@@ -121,10 +123,8 @@ hipError_t launch_deposit_xi(const double *xi, long long np, int n, double *M, h
 hipError_t launch_node_shifts(const double *phi, double *s3, int n, hipStream_t s);
 hipError_t launch_deposit_adj(const double *xi, long long np, int n, const double *s3, const double *Mbar,
                               double *sbar, double *gpos, double gscale, hipStream_t s);
-// y += alpha x, X = double or float; with alpha_dev != null alpha is read there
-template <typename X>
-hipError_t launch_axpy(double *y, const X *x, double alpha, long n3, hipStream_t s,
-                       const double *alpha_dev = nullptr);
+// y += alpha x
+hipError_t launch_axpy(double *y, const double *x, double alpha, long n3, hipStream_t s);
 // y += sign * (*sum / n3)
 hipError_t launch_add_mean(double *y, const double *sum, double sign, long n3, hipStream_t s);
 // delta = -L7 phi; phi_out = phi * h2 (if non-null); partials K=3: min det, min lambda0, max delta
@@ -200,6 +200,13 @@ bool resrestrict25_supported(int n);
 template <typename T>
 hipError_t launch_resrestrict25(const T *u, const T *a, const T *b, T *c, int n, T scale, T a_min, hipStream_t s);
 
+// The directions before p_old whose solution updates are still due (at most
+// two); a direction pass (with u and ks) applies them before p_old's.
+template <typename P>
+struct Older {
+    int count = 0;
+    const P *p[2] = {nullptr, nullptr};  // one and two steps before p_old
+};
 // P: storage of p_old and p_new (double, or float with an FP32 z: p_new is
 // rounded to FP32 as it is formed and q = A p_new uses the rounded value).
 // With ks != null, beta = -ks[KS_ALPHA] ks[KS_ZQ] / ks[KS_RZ_OLD] and alpha_u =
@@ -207,7 +214,7 @@ hipError_t launch_resrestrict25(const T *u, const T *a, const T *b, T *c, int n,
 template <typename Z, typename P>
 hipError_t launch_direction25(const Z *z, const P *p_old, P *p_new, const double *a, double *q, double beta, int n,
                               double a_min, bool first, double *u, double alpha_u, const double *ks, Part &p,
-                              hipStream_t s);
+                              hipStream_t s, const Older<P> &older = {});
 
 hipError_t launch_residual_norm(const double *u, const double *a, const double *b, double *r, float *r32, int n,
                                 double a_min, Part &p, hipStream_t s);
@@ -237,7 +244,13 @@ hipError_t launch_direction(const Z *z, const double *p_old, double *p_new, cons
 bool direction_grouped_supported(int n);
 template <typename Z>
 hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
-                                    double a_min, bool first, double *u, const double *ks, Part &p, hipStream_t s);
+                                    double a_min, bool first, double *u, const double *ks, Part &p, hipStream_t s,
+                                    const Older<double> &older = {});
+// u += the due updates ks[alpha] p of p_old and the older directions, oldest
+// first
+template <typename P>
+hipError_t launch_due_updates(double *u, const P *p_old, const Older<P> &older, const double *ks, long n3,
+                              hipStream_t s);
 // u += alpha p (if u != null); r -= alpha q; partial K=1: sum r^2; r32 = (float) r if r32 != null.
 // With ks != null: alpha = ks[KS_RZ] / ks[KS_PQ], and the kernel stores it in
 // ks[KS_ALPHA] and ks[KS_RZ] in ks[KS_RZ_OLD].  pq with blocks > 0: the K=1

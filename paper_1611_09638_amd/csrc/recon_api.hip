@@ -721,10 +721,10 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
         else HIPCHK(launch_dots_zr_zq<double>(ctx->z, ctx->r, nullptr, n3, ctx->part, ctx->stream));
         bool first = true;
         // Streaming levels form the new direction out of place, fused with its
-        // operator product; it alternates between p and t (idle during a solve),
-        // stored in FP32 when the preconditioner is FP32.  The solution update
-        // u += alpha p of one step is deferred into the next direction pass there
-        // (it reads p anyway), and applied after the loop for the last step.
+        // operator product, stored in FP32 when the preconditioner is FP32.  The
+        // solution update u += alpha p of a step is deferred into a later
+        // direction pass there (which reads the last p anyway), and applied
+        // after the loop for the last ones.
         const bool stream = use_stream<double>(n) && (!Kf || full25_supported(n));
         // Small grids: the direction and the residual update fold the partials
         // of the sums they need themselves (dots and pq, in separate halves of
@@ -739,32 +739,59 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
             HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
             dots.blocks = 0;
         }
-        double *pc = ctx->p, *pn = ctx->t;
+        // Out-of-place directions take the next of a ring of buffers, so the
+        // solution updates of up to `most` steps can wait and be applied in one
+        // pass over u: p, t and dphi (t and dphi are idle during a solve) hold
+        // three FP64 directions, p and t four in FP32 (by halves).  At 128^3 and
+        // above the loop streams memory, and one update a step costs it two of
+        // the eight to twelve passes over fields that a step makes outside the
+        // preconditioner.
         auto f32 = [](double *x) { return reinterpret_cast<float *>(x); };
-        bool due = false;
+        const bool low = mixed && stream;  // directions stored in FP32
+        const bool later = grouped || (stream && !Kf);
+        const int slots = later ? (low ? 4 : 3) : 2, most = slots - 1;
+        double *ring[4] = {ctx->p, ctx->t, ctx->dphi, nullptr};
+        if (low && later) {
+            ring[2] = reinterpret_cast<double *>(f32(ctx->p) + n3);
+            ring[3] = reinterpret_cast<double *>(f32(ctx->t) + n3);
+        }
+        int at = 0, pend = 0;  // the current direction's slot; updates due, its own among them
+        double *pc = ring[0], *pn = ring[1];
+        auto next = [&]() {
+            at = (at + 1) % slots;
+            pc = ring[at];
+            pn = ring[(at + 1) % slots];
+        };
+        auto older = [&](auto tag) {
+            using P = decltype(tag);
+            Older<P> o;
+            o.count = pend > 0 ? pend - 1 : 0;
+            for (int x = 0; x < o.count; ++x)
+                o.p[x] = reinterpret_cast<const P *>(ring[(at + slots - 1 - x) % slots]);
+            return o;
+        };
         // residual norms: the last one seen and the next one extrapolated
         double rn_last = 0.0, rn_next = 0.0;
         while (true) {
+            // the due updates are applied when the ring is full
+            double *ud = pend == most ? ctx->u : nullptr;
             if (stream && Kf) {
-                double *ud = due ? ctx->u : nullptr;
                 if (mixed)
                     HIPCHK(launch_full_direction25(ctx->L32.u[0], f32(pc), f32(pn), *Kf, ctx->q, 0.0, n,
                                                    ctx->cfg.a_min, first, ud, 0.0, ks, ctx->part, ctx->stream));
                 else
                     HIPCHK(launch_full_direction25(ctx->z, pc, pn, *Kf, ctx->q, 0.0, n, ctx->cfg.a_min, first, ud,
                                                    0.0, ks, ctx->part, ctx->stream));
-                due = false;
-                std::swap(pc, pn);
+                next();
             } else if (stream) {
-                double *ud = due ? ctx->u : nullptr;
                 if (mixed)
                     HIPCHK(launch_direction25(ctx->L32.u[0], f32(pc), f32(pn), a0, ctx->q, 0.0, n, ctx->cfg.a_min,
-                                              first, ud, 0.0, ks, ctx->part, ctx->stream));
+                                              first, ud, 0.0, ks, ctx->part, ctx->stream,
+                                              ud ? older(float()) : Older<float>()));
                 else
                     HIPCHK(launch_direction25(ctx->z, pc, pn, a0, ctx->q, 0.0, n, ctx->cfg.a_min, first, ud, 0.0, ks,
-                                              ctx->part, ctx->stream));
-                due = false;
-                std::swap(pc, pn);
+                                              ctx->part, ctx->stream, ud ? older(double()) : Older<double>()));
+                next();
             } else if (Kf) {
                 if (mixed) HIPCHK(launch_update_p<float>(ctx->L32.u[0], pc, 0.0, n3, first, ks, ctx->stream));
                 else HIPCHK(launch_update_p<double>(ctx->z, pc, 0.0, n3, first, ks, ctx->stream));
@@ -776,17 +803,17 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
                 else
                     HIPCHK(launch_direction<double>(ctx->z, pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first, ks, dots, pq,
                                                     ctx->stream));
-                std::swap(pc, pn);
+                next();
             } else if (grouped) {
-                double *ud = due ? ctx->u : nullptr;
                 if (mixed)
                     HIPCHK(launch_direction_grouped<float>(ctx->L32.u[0], pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first,
-                                                           ud, ks, pq, ctx->stream));
+                                                           ud, ks, pq, ctx->stream,
+                                                           ud ? older(double()) : Older<double>()));
                 else
                     HIPCHK(launch_direction_grouped<double>(ctx->z, pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first, ud,
-                                                            ks, pq, ctx->stream));
-                due = false;
-                std::swap(pc, pn);
+                                                            ks, pq, ctx->stream,
+                                                            ud ? older(double()) : Older<double>()));
+                next();
             } else if (mixed) {
                 HIPCHK(launch_update_pq<float>(ctx->L32.u[0], a0, pc, ctx->q, 0.0, n, ctx->cfg.a_min, first, ks,
                                                ctx->part, ctx->stream));
@@ -796,7 +823,8 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
             }
             first = false;
             if (!fold) HIPCHK(reduce_finalize(grouped ? pq : ctx->part, sums, ks + KS_PQ, ctx->stream));
-            due = stream || grouped;
+            const bool due = stream || grouped;
+            if (due) pend = ud ? 1 : pend + 1;
             HIPCHK(launch_update_ur(due ? nullptr : ctx->u, ctx->r, pc, ctx->q, 0.0, r32, n3, ks, ctx->part,
                                     ctx->stream, fold ? &pq : nullptr));
             // The stop test needs ||r|| on the host.  When this step cannot be
@@ -828,8 +856,8 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
             if (fold) dots = ctx->part;
             else HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
         }
-        if (due && mixed && stream) HIPCHK(launch_axpy(ctx->u, f32(pc), 0.0, n3, ctx->stream, ks + KS_ALPHA));
-        else if (due) HIPCHK(launch_axpy(ctx->u, pc, 0.0, n3, ctx->stream, ks + KS_ALPHA));
+        if (pend && low) HIPCHK(launch_due_updates<float>(ctx->u, f32(pc), older(float()), ks, n3, ctx->stream));
+        else if (pend) HIPCHK(launch_due_updates<double>(ctx->u, pc, older(double()), ks, n3, ctx->stream));
     }
     // mean-free solution, then the true residual
     HIPCHK(launch_sum(ctx->u, n3, ctx->part, ctx->stream));

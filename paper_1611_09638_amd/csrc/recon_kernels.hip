@@ -415,22 +415,16 @@ hipError_t launch_pd_trials(const double *phi, const double *dphi, int n, int j0
     return hipGetLastError();
 }
 
-template <typename X>
-__global__ void k_axpy(double *__restrict__ y, const X *__restrict__ x, double alpha, long n3,
-                       const double *__restrict__ alpha_dev)
+__global__ void k_axpy(double *__restrict__ y, const double *__restrict__ x, double alpha, long n3)
 {
-    if (alpha_dev) alpha = *alpha_dev;
-    for (long p = blockIdx.x * 256L + threadIdx.x; p < n3; p += 256L * gridDim.x) y[p] += alpha * (double)x[p];
+    for (long p = blockIdx.x * 256L + threadIdx.x; p < n3; p += 256L * gridDim.x) y[p] += alpha * x[p];
 }
 
-template <typename X>
-hipError_t launch_axpy(double *y, const X *x, double alpha, long n3, hipStream_t s, const double *alpha_dev)
+hipError_t launch_axpy(double *y, const double *x, double alpha, long n3, hipStream_t s)
 {
-    k_axpy<X><<<flat_blocks(n3), 256, 0, s>>>(y, x, alpha, n3, alpha_dev);
+    k_axpy<<<flat_blocks(n3), 256, 0, s>>>(y, x, alpha, n3);
     return hipGetLastError();
 }
-template hipError_t launch_axpy<double>(double *, const double *, double, long, hipStream_t, const double *);
-template hipError_t launch_axpy<float>(double *, const float *, double, long, hipStream_t, const double *);
 
 // y += sign * mean, the mean of a field whose sum over n3 nodes is *sum
 __global__ void k_add_mean(double *__restrict__ y, const double *__restrict__ sum, double sign, long n3)
@@ -909,6 +903,8 @@ __global__ void __launch_bounds__(U ? 256 : 1024) k_update_ur(double *__restrict
         alpha = rz / d[0];
         // only this kernel's other lanes read ks, and only KS_RZ and KS_PQ
         if (blockIdx.x == 0 && threadIdx.x == 0) {
+            ks[KS_ALPHA2] = ks[KS_ALPHA1];
+            ks[KS_ALPHA1] = ks[KS_ALPHA];
             ks[KS_ALPHA] = alpha;
             ks[KS_RZ_OLD] = rz;
         }
@@ -988,6 +984,37 @@ hipError_t launch_update_ur(double *u, double *r, const double *pv, const double
     p.k = 1;
     return hipGetLastError();
 }
+
+// What is left due when the conjugate-gradient loop ends: one read and write of
+// u for one, two or three directions (N).
+template <typename P, int N>
+__global__ void k_due_updates(double *__restrict__ u, const P *__restrict__ p0, const P *__restrict__ p1,
+                              const P *__restrict__ p2, const double *__restrict__ ks, long n3)
+{
+    const double a0 = ks[KS_ALPHA], a1 = ks[KS_ALPHA1], a2 = ks[KS_ALPHA2];
+    for (long p = blockIdx.x * 256L + threadIdx.x; p < n3; p += 256L * gridDim.x) {
+        double x = u[p];
+        if (N > 2) x += a2 * (double)p2[p];
+        if (N > 1) x += a1 * (double)p1[p];
+        u[p] = x + a0 * (double)p0[p];
+    }
+}
+
+template <typename P>
+hipError_t launch_due_updates(double *u, const P *p_old, const Older<P> &older, const double *ks, long n3,
+                              hipStream_t s)
+{
+    const int nb = flat_blocks(n3);
+    if (older.count == 0) k_due_updates<P, 1><<<nb, 256, 0, s>>>(u, p_old, nullptr, nullptr, ks, n3);
+    else if (older.count == 1) k_due_updates<P, 2><<<nb, 256, 0, s>>>(u, p_old, older.p[0], nullptr, ks, n3);
+    else if (older.count == 2) k_due_updates<P, 3><<<nb, 256, 0, s>>>(u, p_old, older.p[0], older.p[1], ks, n3);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+template hipError_t launch_due_updates<double>(double *, const double *, const Older<double> &, const double *, long,
+                                               hipStream_t);
+template hipError_t launch_due_updates<float>(double *, const float *, const Older<float> &, const double *, long,
+                                              hipStream_t);
 
 template <typename Z>
 __global__ void k_add_correction(double *__restrict__ u, const Z *__restrict__ z, long n3)

@@ -56,7 +56,13 @@ __device__ __forceinline__ void lds_fence_barrier()
 // back before they have left the caches; 512^3 solves 0.7-1% faster).
 // FIRST (direction only): the first Krylov step, p = z, p_old not read.
 // UPD (direction only, not FIRST): also ug += alpha_u xin, the solution update
-// of the previous Krylov step, deferred to this pass, which reads p_old anyway.
+// of the previous Krylov step, deferred to this pass, which reads p_old anyway;
+// UPD = 2, 3: those of the one or two steps before too (xo1, xo2, oldest
+// first, each rounded as a pass of its own would), so u is read and written in
+// every second or third step only.  512^3 with FP32 directions, a read and a
+// write of u in each step or in every third: the solve 526 -> 512 ms; 256^3
+// 80.4 -> 78.9 (a direction without the update 100 us, with one 147, with three
+// 176); FP64 directions at 512^3, in every second step, 742 -> 732 ms.
 // P (direction only): storage type of p_old and p_new.  With P = float the new
 // direction is rounded to FP32 as it is formed, so the stored p_new is exactly
 // the operand of A and of the later solution update.
@@ -70,14 +76,18 @@ __global__ void __launch_bounds__(NT)
     k_flux25(const P *__restrict__ xin, const Z *__restrict__ zg, const T *__restrict__ ag,
              const T *__restrict__ bg, T *__restrict__ out, float *__restrict__ out32, P *__restrict__ pout, int n,
              int ci, T scale, T a_min, T beta, double *part, double *__restrict__ ug, double alpha_u,
-             const double *__restrict__ ks, int ipb = 0)
+             const double *__restrict__ ks, int ipb = 0, const P *__restrict__ xo1 = nullptr,
+             const P *__restrict__ xo2 = nullptr)
 {
+    double alpha1 = 0.0, alpha2 = 0.0;
     static_assert(!GRP || (MODE == S25_DIRECTION && TK == 64 && TJ % 4 == 0), "a wave is a row of 64 nodes");
     if constexpr (MODE == S25_DIRECTION && !FIRST) {
         // the step sizes of the conjugate-gradient loop, formed on the device
         if (ks) {
             beta = -ks[KS_ALPHA] * ks[KS_ZQ] / ks[KS_RZ_OLD];
             alpha_u = ks[KS_ALPHA];
+            if (UPD > 1) alpha1 = ks[KS_ALPHA1];
+            if (UPD > 2) alpha2 = ks[KS_ALPHA2];
         }
     }
     static_assert(!UPD || (MODE == S25_DIRECTION && !FIRST), "the deferred update needs p_old");
@@ -140,7 +150,7 @@ __global__ void __launch_bounds__(NT)
     // operand is formed when the plane is deposited, so a wave waits for
     // these loads only there, two planes after issuing them.
     Z rz[2][HAS_Z ? LU : 1];
-    P rx[2][HAS_X ? LU : 1], rq[2][UPD ? RS : 1];
+    P rx[2][HAS_X ? LU : 1], rq[2][UPD ? RS : 1], rq1[2][UPD > 1 ? RS : 1], rq2[2][UPD > 2 ? RS : 1];
     T ra[2][LU], rb[2][HAS_B ? RS : 1];
     double ru[2][UPD ? RS : 1];
     auto fetch = [&](int set, int p) {
@@ -162,6 +172,8 @@ __global__ void __launch_bounds__(NT)
             for (int r = 0; r < RS; ++r) {
                 ru[set][r] = ug[bb + gN[r]];
                 rq[set][r] = xin[bb + gN[r]];
+                if constexpr (UPD > 1) rq1[set][r] = xo1[bb + gN[r]];
+                if constexpr (UPD > 2) rq2[set][r] = xo2[bb + gN[r]];
             }
         }
     };
@@ -222,7 +234,12 @@ __global__ void __launch_bounds__(NT)
                 store(acc, &out[g]);
                 if constexpr (GRP) vg[r] += xc * acc;
                 else v += xc * acc;
-                if constexpr (UPD) store(ru[set][r] + alpha_u * (double)rq[set][r], &ug[g]);
+                if constexpr (UPD) {
+                    double x = ru[set][r];
+                    if constexpr (UPD > 2) x += alpha2 * (double)rq2[set][r];
+                    if constexpr (UPD > 1) x += alpha1 * (double)rq1[set][r];
+                    store(x + alpha_u * (double)rq[set][r], &ug[g]);
+                }
             }
             xd[r] = xc;
             hd[r] = hc;
@@ -379,9 +396,11 @@ bool direction_grouped_supported(int n) { return n >= 128 && n % 64 == 0 && grou
 
 template <typename Z>
 hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
-                                    double a_min, bool first, double *u, const double *ks, Part &p, hipStream_t s)
+                                    double a_min, bool first, double *u, const double *ks, Part &p, hipStream_t s,
+                                    const Older<double> &older)
 {
     constexpr int TJ = 16, NT = 512;
+    if (older.count < 0 || older.count > 1 || (older.count && !u)) return hipErrorInvalidValue;
     if (!direction_grouped_supported(n) || p_old == p_new || (u && (first || p_old == u || p_new == u || u == q)))
         return hipErrorInvalidValue;
     const int ipb = shape3(n).ipb, ci = grouped_chunk(n), nb = (n / 64) * (n / TJ) * (n / ci);
@@ -389,13 +408,15 @@ hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_n
     if (rows > kPartCap / 2) return hipErrorInvalidValue;
 #define RECON_GRP(FIRST, UPD, G)                                                                                   \
     k_flux25<double, Z, S25_DIRECTION, TJ, NT, 64, FIRST, UPD, double, G><<<nb, NT, 0, s>>>(                       \
-        p_old, z, a, nullptr, q, nullptr, p_new, n, ci, 1.0, a_min, 0.0, p.part, u, 0.0, ks, ipb)
+        p_old, z, a, nullptr, q, nullptr, p_new, n, ci, 1.0, a_min, 0.0, p.part, u, 0.0, ks, ipb, older.p[0])
     if (n < 256) {
         if (first) RECON_GRP(1, 0, 2);
+        else if (older.count) RECON_GRP(0, 2, 2);
         else if (u) RECON_GRP(0, 1, 2);
         else RECON_GRP(0, 0, 2);
     } else {
         if (first) RECON_GRP(1, 0, 1);
+        else if (older.count) RECON_GRP(0, 2, 1);
         else if (u) RECON_GRP(0, 1, 1);
         else RECON_GRP(0, 0, 1);
     }
@@ -406,17 +427,19 @@ hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_n
 }
 template hipError_t launch_direction_grouped<double>(const double *, const double *, double *, const double *,
                                                      double *, int, double, bool, double *, const double *, Part &,
-                                                     hipStream_t);
+                                                     hipStream_t, const Older<double> &);
 template hipError_t launch_direction_grouped<float>(const float *, const double *, double *, const double *, double *,
-                                                    int, double, bool, double *, const double *, Part &, hipStream_t);
+                                                    int, double, bool, double *, const double *, Part &, hipStream_t,
+                                                    const Older<double> &);
 
 template <typename Z, typename P>
 hipError_t launch_direction25(const Z *z, const P *p_old, P *p_new, const double *a, double *q, double beta, int n,
                               double a_min, bool first, double *u, double alpha_u, const double *ks, Part &p,
-                              hipStream_t s)
+                              hipStream_t s, const Older<P> &older)
 {
     using C = S25Launch<double, S25_DIRECTION>;
     const void *po = p_old;
+    if (older.count < 0 || older.count > 2 || (older.count && (!u || !ks))) return hipErrorInvalidValue;
     if (!s25_fits<C>(n) || po == p_new || (u && (first || po == u || (void *)p_new == u || u == q)))
         return hipErrorInvalidValue;
     const int ci = s25_chunk<C>(n), nb = s25_blocks<C>(n, ci);
@@ -424,6 +447,13 @@ hipError_t launch_direction25(const Z *z, const P *p_old, P *p_new, const double
     if (first)
         k_flux25<double, Z, S25_DIRECTION, C::TJ, C::NT, C::TK, 1, 0, P><<<nb, C::NT, 0, s>>>(
             p_old, z, a, nullptr, q, nullptr, p_new, n, ci, 1.0, a_min, beta, p.part, nullptr, 0.0, nullptr);
+    else if (older.count == 2)
+        k_flux25<double, Z, S25_DIRECTION, C::TJ, C::NT, C::TK, 0, 3, P><<<nb, C::NT, 0, s>>>(
+            p_old, z, a, nullptr, q, nullptr, p_new, n, ci, 1.0, a_min, beta, p.part, u, alpha_u, ks, 0, older.p[0],
+            older.p[1]);
+    else if (older.count == 1)
+        k_flux25<double, Z, S25_DIRECTION, C::TJ, C::NT, C::TK, 0, 2, P><<<nb, C::NT, 0, s>>>(
+            p_old, z, a, nullptr, q, nullptr, p_new, n, ci, 1.0, a_min, beta, p.part, u, alpha_u, ks, 0, older.p[0]);
     else if (u)
         k_flux25<double, Z, S25_DIRECTION, C::TJ, C::NT, C::TK, 0, 1, P><<<nb, C::NT, 0, s>>>(
             p_old, z, a, nullptr, q, nullptr, p_new, n, ci, 1.0, a_min, beta, p.part, u, alpha_u, ks);
@@ -443,12 +473,12 @@ template hipError_t launch_residual25<double>(const double *, const double *, co
                                               double, hipStream_t);
 template hipError_t launch_direction25<float, double>(const float *, const double *, double *, const double *,
                                                       double *, double, int, double, bool, double *, double,
-                                                      const double *, Part &, hipStream_t);
+                                                      const double *, Part &, hipStream_t, const Older<double> &);
 template hipError_t launch_direction25<float, float>(const float *, const float *, float *, const double *, double *,
                                                      double, int, double, bool, double *, double, const double *,
-                                                     Part &, hipStream_t);
+                                                     Part &, hipStream_t, const Older<float> &);
 template hipError_t launch_direction25<double, double>(const double *, const double *, double *, const double *,
                                                        double *, double, int, double, bool, double *, double,
-                                                       const double *, Part &, hipStream_t);
+                                                       const double *, Part &, hipStream_t, const Older<double> &);
 
 }  // namespace recon

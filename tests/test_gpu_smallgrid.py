@@ -154,3 +154,38 @@ def test_grouped_direction_sums_like_the_gather(torch_cuda, n, cn, mixed):
     want -= want.mean()
     # the stage steps' sums (torch's) differ from the loop's by about n^1.5 ulp
     assert float((u - want).norm() / want.norm()) < 1e-11
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("n,cn,mixed", [(128, 8, False), (128, 8, True), (256, 16, False), (256, 16, True)])
+def test_deferred_solution_updates(torch_cuda, n, cn, mixed, steps):
+    """Solution updates applied two steps (FP64 directions) or three steps
+    (FP32 directions, 256^3 mixed) at a time, for every count left due when the
+    loop ends: u against the sum of alpha p of a loop made of stage calls.  The
+    k-th update is about 0.2^k of u, the fifth 3e-4; the loops differ by the
+    rounding of their sums (1e-14) in FP64, and in mixed mode by the rounding
+    of z and p to FP32 (1e-7 a step) after the mean that only one of them has
+    taken off."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(n + 7)
+    a = torch.exp(torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64))
+    b = torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64)
+    b -= b.mean()
+    kw = dict(coarse_n=cn, precision=binding.MIXED if mixed else binding.FP64)
+    u, cycles, _ = binding.Recon(n, binding.Config(fixed_cycles=steps, **kw)).mg_solve(a, b)
+    assert cycles == steps
+    one = binding.Recon(n, binding.Config(solver=binding.SOLVER_VCYCLE, fixed_cycles=1, **kw))
+    r, want, p, q, alpha, rz = b.clone(), torch.zeros_like(b), None, None, 0.0, 0.0
+    for step in range(steps):
+        z, _, _ = one.mg_solve(a, r)
+        old, rz = rz, float((z * r).sum())
+        p = z if step == 0 else z - alpha * float((z * q).sum()) / old * p
+        if mixed and n == 256:
+            p = p.float().double()
+        _, q, pq = one.direction(p, None, a, 0.0, first=True, variant=1)
+        alpha = rz / pq
+        want += alpha * p
+        r -= alpha * q
+    want -= want.mean()
+    assert float((u - want).norm() / want.norm()) < (1e-5 if mixed else 1e-10)

@@ -48,18 +48,26 @@ __device__ __forceinline__ void lds_barrier()
 //                     out = L_K x, sum x out
 // MODE F25_APPLY:     out = L_K x (x = xin, P = double; no reduction)
 // FIRST: the first Krylov step (p = z, p_old not read).  UPD (not FIRST):
-// also ug += alpha_u xin, the previous step's solution update.  With ks,
-// beta and alpha_u come from the device scalars of the Krylov loop.
-template <typename Z, typename P, int MODE, int TJ, int TK, int NT, int FIRST = 0, int UPD = 0>
+// also ug += alpha_u xin, the previous step's solution update, and UPD = 2, 3
+// those of the one or two steps before (xo1, xo2), oldest first.  With ks,
+// beta and the step sizes come from the device scalars of the Krylov loop.
+// GRP: the partial sums are rows of 64 x 4 nodes and ipb planes, as the gather
+// kernels leave them (a wave is a row of 64); else one partial per workgroup.
+template <typename Z, typename P, int MODE, int TJ, int TK, int NT, int FIRST = 0, int UPD = 0, int GRP = 0>
 __global__ void __launch_bounds__(NT)
     k_full25(const P *__restrict__ xin, const Z *__restrict__ zg, const double *__restrict__ bg, MassTensor K,
              double *__restrict__ out, float *__restrict__ out32, P *__restrict__ pout, int n, int ci, double beta,
-             double a_min, double *part, double *__restrict__ ug, double alpha_u, const double *__restrict__ ks)
+             double a_min, double *part, double *__restrict__ ug, double alpha_u, const double *__restrict__ ks,
+             int ipb = 0, const P *__restrict__ xo1 = nullptr, const P *__restrict__ xo2 = nullptr)
 {
+    static_assert(!GRP || (MODE != F25_APPLY && TK == 64 && TJ % 4 == 0), "a wave is a row of 64 nodes");
+    double alpha1 = 0.0, alpha2 = 0.0;
     if constexpr (MODE == F25_DIRECTION && !FIRST) {
         if (ks) {
             beta = -ks[KS_ALPHA] * ks[KS_ZQ] / ks[KS_RZ_OLD];
             alpha_u = ks[KS_ALPHA];
+            if (UPD > 1) alpha1 = ks[KS_ALPHA1];
+            if (UPD > 2) alpha2 = ks[KS_ALPHA2];
         }
     }
     static_assert(!UPD || (MODE == F25_DIRECTION && !FIRST), "the deferred update needs p_old");
@@ -118,7 +126,8 @@ __global__ void __launch_bounds__(NT)
     // column values K.xx, K.xy, K.xz of plane p + 2, and b (or u, p_old) of
     // plane p + 1 at this thread's nodes
     double rf[LU], rk[5][LU], rcx[RS], rcy[RS], rcz[RS];
-    double rb[HAS_B ? RS : 1], ru[UPD ? RS : 1], rq[UPD ? RS : 1];
+    double rb[HAS_B ? RS : 1], ru[UPD ? RS : 1];
+    P rq[UPD ? RS : 1], rq1[UPD > 1 ? RS : 1], rq2[UPD > 2 ? RS : 1];
     auto fetch = [&](int p) {  // p: the plane computed next
         const size_t bf = plane(p + 2), bk = plane(p + 1);
 #pragma unroll
@@ -141,7 +150,9 @@ __global__ void __launch_bounds__(NT)
 #pragma unroll
             for (int r = 0; r < RS; ++r) {
                 ru[r] = ug[bk + gN[r]];
-                rq[r] = (double)xin[bk + gN[r]];
+                rq[r] = xin[bk + gN[r]];
+                if constexpr (UPD > 1) rq1[r] = xo1[bk + gN[r]];
+                if constexpr (UPD > 2) rq2[r] = xo2[bk + gN[r]];
             }
         }
     };
@@ -149,8 +160,17 @@ __global__ void __launch_bounds__(NT)
     // column queues at this thread's nodes: K.xx at p - 1, p, p + 1; K.xy and
     // K.xz at p - 1 and p + 1; b (or u, p_old) at p
     double qxx0[RS], qxx1[RS], qxx2[RS], qxym[RS], qxyp[RS], qxzm[RS], qxzp[RS];
-    double cb[HAS_B ? RS : 1], cu[UPD ? RS : 1], cq[UPD ? RS : 1];
-    double v = 0.0;
+    double cb[HAS_B ? RS : 1], cu[UPD ? RS : 1];
+    P cq[UPD ? RS : 1], cq1[UPD > 1 ? RS : 1], cq2[UPD > 2 ? RS : 1];
+    double v = 0.0, vg[GRP ? RS : 1];
+    __shared__ double sums[2][GRP ? TJ : 1];
+    if constexpr (GRP)
+#pragma unroll
+        for (int r = 0; r < RS; ++r) vg[r] = 0.0;
+    auto add = [&](int r, double x, double y) {
+        if constexpr (GRP) vg[r] += x * y;
+        else v += x * y;
+    };
 
     // prologue: operand planes i0 - 1, i0, i0 + 1 and K plane i0 resident
     {
@@ -176,7 +196,9 @@ __global__ void __launch_bounds__(NT)
             if constexpr (HAS_B) cb[r] = bg[b0 + gN[r]];
             if constexpr (UPD) {
                 cu[r] = ug[b0 + gN[r]];
-                cq[r] = (double)xin[b0 + gN[r]];
+                cq[r] = xin[b0 + gN[r]];
+                if constexpr (UPD > 1) cq1[r] = xo1[b0 + gN[r]];
+                if constexpr (UPD > 2) cq2[r] = xo2[b0 + gN[r]];
             }
         }
     }
@@ -220,14 +242,19 @@ __global__ void __launch_bounds__(NT)
                 const double rv = cb[r] - acc;
                 out[g] = rv;
                 if (out32) out32[g] = (float)rv;
-                v += rv * rv;
+                add(r, rv, rv);
             } else if constexpr (MODE == F25_APPLY) {
                 out[g] = acc;
             } else {
                 pout[g] = (P)s.c;
                 out[g] = acc;
-                v += s.c * acc;
-                if constexpr (UPD) ug[g] = cu[r] + alpha_u * cq[r];
+                add(r, s.c, acc);
+                if constexpr (UPD) {
+                    double x = cu[r];
+                    if constexpr (UPD > 2) x += alpha2 * (double)cq2[r];
+                    if constexpr (UPD > 1) x += alpha1 * (double)cq1[r];
+                    ug[g] = x + alpha_u * (double)cq[r];
+                }
             }
             // advance the column queues to plane p + 1
             qxx0[r] = qxx1[r];
@@ -241,8 +268,23 @@ __global__ void __launch_bounds__(NT)
             if constexpr (UPD) {
                 cu[r] = ru[r];
                 cq[r] = rq[r];
+                if constexpr (UPD > 1) cq1[r] = rq1[r];
+                if constexpr (UPD > 2) cq2[r] = rq2[r];
             }
         }
+        // a finished group's rows: two sets, so the next group's do not meet
+        // the reads behind this plane's barrier
+        const bool ends = GRP && ((p + 1) % ipb == 0 || p + 1 == n);
+        const int set = GRP ? (p / ipb) & 1 : 0;
+        if constexpr (GRP)
+            if (ends) {
+#pragma unroll
+                for (int r = 0; r < RS; ++r) {
+                    const double x = wave_reduce<RED_SUM>(vg[r]);
+                    if ((tid & 63) == 0) sums[set][(tid + r * NT) / 64] = x;
+                    vg[r] = 0.0;
+                }
+            }
         // operand plane p + 2 into the slot of p - 2, K plane p + 1 into the
         // slot of p - 1: both last read before the previous barrier
 #pragma unroll
@@ -252,9 +294,15 @@ __global__ void __launch_bounds__(NT)
             for (int f = 0; f < 5; ++f) sK[f][kc ^ 1][dL[r]] = rk[f][r];
         }
         lds_barrier();
+        if constexpr (GRP)
+            if (ends && tid < TJ / 4) {
+                double x = sums[set][4 * tid];
+                for (int w = 1; w < 4; ++w) x += sums[set][4 * tid + w];
+                part[tk + (size_t)tiles_k * (j0 / 4 + tid + (size_t)(n / 4) * (p / ipb))] = x;
+            }
         fetch(p + 1);
     }
-    if constexpr (MODE != F25_APPLY) {
+    if constexpr (MODE != F25_APPLY && !GRP) {
         double vv[1] = {v};
         block_reduce_store<1, RED_SUM>(vv, part, blockIdx.x);
     }
@@ -283,16 +331,40 @@ int f25_blocks(int n, int ci) { return (n / F25Launch::TK) * (n / F25Launch::TJ)
 
 bool full25_supported(int n) { return f25_fits(n); }
 
+// Launches that leave the gather kernels' partials, from 128^3 (below, the
+// launch has fewer than two workgroups per CU): chunks are whole groups of ipb
+// planes, at most 8 below 256^3 (128^3: 512 workgroups) and 24 above.  A gather
+// fetches 40 operands a node through the vector caches; here they come from
+// LDS.  128^3 with an FP32 preconditioner: product and direction 60 + 12 us as
+// gather launches, 37 streamed (45 with two solution updates, 7 us a step
+// less in the residual update); the residual 61 -> 39.5.  Whole
+// reconstructions: 128^3 36.8 -> 31.8 ms, 192^3 101 -> 80, 320^3 405 -> 300.
+int f25_grouped_chunk(int n)
+{
+    const int ipb = shape3(n).ipb, most = n < 256 ? 8 : 24;
+    int ci = 0;
+    for (int c = 1; c <= n; ++c)
+        if (n % c == 0 && c % ipb == 0 && (ci == 0 || c <= most)) ci = c;
+    return ci;
+}
+
+bool full_grouped_supported(int n) { return n >= 128 && f25_fits(n) && f25_grouped_chunk(n) > 0; }
+
 hipError_t launch_full_residual_norm25(const MassTensor &K, const double *u, const double *b, double *r, float *r32,
-                                       int n, double a_min, Part &p, hipStream_t s)
+                                       int n, double a_min, Part &p, hipStream_t s, bool grouped)
 {
     using C = F25Launch;
-    if (!f25_fits(n)) return hipErrorInvalidValue;
-    const int ci = f25_chunk(n), nb = f25_blocks(n, ci);
-    if ((long)nb > kPartCap) return hipErrorInvalidValue;
-    k_full25<double, double, F25_RESNORM, C::TJ, C::TK, C::NT><<<nb, C::NT, 0, s>>>(
-        u, nullptr, b, K, r, r32, nullptr, n, ci, 0.0, a_min, p.part, nullptr, 0.0, nullptr);
-    p.blocks = nb;
+    if (!f25_fits(n) || (grouped && !full_grouped_supported(n))) return hipErrorInvalidValue;
+    const int ci = grouped ? f25_grouped_chunk(n) : f25_chunk(n), nb = f25_blocks(n, ci), ipb = shape3(n).ipb;
+    const long rows = grouped ? (long)(n / 64) * (n / 4) * ((n + ipb - 1) / ipb) : nb;
+    if (rows > kPartCap) return hipErrorInvalidValue;
+    if (grouped)
+        k_full25<double, double, F25_RESNORM, C::TJ, C::TK, C::NT, 0, 0, 1><<<nb, C::NT, 0, s>>>(
+            u, nullptr, b, K, r, r32, nullptr, n, ci, 0.0, a_min, p.part, nullptr, 0.0, nullptr, ipb);
+    else
+        k_full25<double, double, F25_RESNORM, C::TJ, C::TK, C::NT><<<nb, C::NT, 0, s>>>(
+            u, nullptr, b, K, r, r32, nullptr, n, ci, 0.0, a_min, p.part, nullptr, 0.0, nullptr);
+    p.blocks = (int)rows;
     p.k = 1;
     return hipGetLastError();
 }
@@ -307,39 +379,76 @@ hipError_t launch_full_apply25(const MassTensor &K, const double *f, double *out
     return hipGetLastError();
 }
 
-template <typename Z, typename P>
-hipError_t launch_full_direction25(const Z *z, const P *p_old, P *p_new, const MassTensor &K, double *q, double beta,
-                                   int n, double a_min, bool first, double *u, double alpha_u, const double *ks,
-                                   Part &p, hipStream_t s)
+namespace {
+
+template <typename Z, typename P, int GRP>
+hipError_t full_direction(const Z *z, const P *p_old, P *p_new, const MassTensor &K, double *q, double beta, int n,
+                                 int ci, double a_min, bool first, double *u, double alpha_u, const double *ks,
+                                 Part &p, hipStream_t s, const Older<P> &older)
 {
     using C = F25Launch;
     const void *po = p_old;
+    if (older.count < 0 || older.count > (sizeof(P) == 8 ? 1 : 2) || (older.count && (!u || !ks)))
+        return hipErrorInvalidValue;
     if (!f25_fits(n) || po == p_new || (u && (first || po == u || (void *)p_new == u || u == q)))
         return hipErrorInvalidValue;
-    const int ci = f25_chunk(n), nb = f25_blocks(n, ci);
-    if ((long)nb > kPartCap) return hipErrorInvalidValue;
-    if (first)
-        k_full25<Z, P, F25_DIRECTION, C::TJ, C::TK, C::NT, 1, 0><<<nb, C::NT, 0, s>>>(
-            p_old, z, nullptr, K, q, nullptr, p_new, n, ci, beta, a_min, p.part, nullptr, 0.0, nullptr);
-    else if (u)
-        k_full25<Z, P, F25_DIRECTION, C::TJ, C::TK, C::NT, 0, 1><<<nb, C::NT, 0, s>>>(
-            p_old, z, nullptr, K, q, nullptr, p_new, n, ci, beta, a_min, p.part, u, alpha_u, ks);
-    else
-        k_full25<Z, P, F25_DIRECTION, C::TJ, C::TK, C::NT, 0, 0><<<nb, C::NT, 0, s>>>(
-            p_old, z, nullptr, K, q, nullptr, p_new, n, ci, beta, a_min, p.part, nullptr, 0.0, ks);
-    p.blocks = nb;
+    const int nb = f25_blocks(n, ci), ipb = shape3(n).ipb;
+    const long rows = GRP ? (long)(n / 64) * (n / 4) * ((n + ipb - 1) / ipb) : nb;
+    if (rows > (GRP ? kPartCap / 2 : kPartCap)) return hipErrorInvalidValue;
+#define RECON_F25(FIRST, UPD)                                                                                      \
+    k_full25<Z, P, F25_DIRECTION, C::TJ, C::TK, C::NT, FIRST, UPD, GRP><<<nb, C::NT, 0, s>>>(                      \
+        p_old, z, nullptr, K, q, nullptr, p_new, n, ci, beta, a_min, p.part, u, alpha_u, ks, ipb, older.p[0],      \
+        older.p[1])
+    if (first) RECON_F25(1, 0);
+    else if (older.count == 2) {
+        if constexpr (sizeof(P) < 8) RECON_F25(0, 3);
+    } else if (older.count == 1) RECON_F25(0, 2);
+    else if (u) RECON_F25(0, 1);
+    else RECON_F25(0, 0);
+#undef RECON_F25
+    p.blocks = (int)rows;
     p.k = 1;
     return hipGetLastError();
 }
 
+}  // namespace
+
+template <typename Z, typename P>
+hipError_t launch_full_direction25(const Z *z, const P *p_old, P *p_new, const MassTensor &K, double *q, double beta,
+                                   int n, double a_min, bool first, double *u, double alpha_u, const double *ks,
+                                   Part &p, hipStream_t s, const Older<P> &older)
+{
+    if (!f25_fits(n)) return hipErrorInvalidValue;
+    return full_direction<Z, P, 0>(z, p_old, p_new, K, q, beta, n, f25_chunk(n), a_min, first, u, alpha_u, ks, p, s,
+                                   older);
+}
+
+template <typename Z>
+hipError_t launch_full_direction_grouped(const Z *z, const double *p_old, double *p_new, const MassTensor &K,
+                                         double *q, int n, double a_min, bool first, double *u, const double *ks,
+                                         Part &p, hipStream_t s, const Older<double> &older)
+{
+    if (!full_grouped_supported(n)) return hipErrorInvalidValue;
+    return full_direction<Z, double, 1>(z, p_old, p_new, K, q, 0.0, n, f25_grouped_chunk(n), a_min, first, u, 0.0, ks,
+                                        p, s, older);
+}
+
 template hipError_t launch_full_direction25<float, float>(const float *, const float *, float *, const MassTensor &,
                                                           double *, double, int, double, bool, double *, double,
-                                                          const double *, Part &, hipStream_t);
+                                                          const double *, Part &, hipStream_t, const Older<float> &);
 template hipError_t launch_full_direction25<float, double>(const float *, const double *, double *,
-                                                           const MassTensor &, double *, double, int, double, bool, double *,
-                                                           double, const double *, Part &, hipStream_t);
+                                                           const MassTensor &, double *, double, int, double, bool,
+                                                           double *, double, const double *, Part &, hipStream_t,
+                                                           const Older<double> &);
 template hipError_t launch_full_direction25<double, double>(const double *, const double *, double *,
-                                                            const MassTensor &, double *, double, int, double, bool, double *,
-                                                            double, const double *, Part &, hipStream_t);
+                                                            const MassTensor &, double *, double, int, double, bool,
+                                                            double *, double, const double *, Part &, hipStream_t,
+                                                            const Older<double> &);
+template hipError_t launch_full_direction_grouped<float>(const float *, const double *, double *, const MassTensor &,
+                                                         double *, int, double, bool, double *, const double *,
+                                                         Part &, hipStream_t, const Older<double> &);
+template hipError_t launch_full_direction_grouped<double>(const double *, const double *, double *,
+                                                          const MassTensor &, double *, int, double, bool, double *,
+                                                          const double *, Part &, hipStream_t, const Older<double> &);
 
 }  // namespace recon

@@ -28,6 +28,14 @@ enum KrylovScalar {
 };
 enum RedOp { RED_SUM = 0, RED_MAX = 1, RED_MIN = 2 };
 
+// The directions before p_old whose solution updates are still due (at most
+// two); a direction pass (with u and ks) applies them before p_old's.
+template <typename P>
+struct Older {
+    int count = 0;
+    const P *p[2] = {nullptr, nullptr};  // one and two steps before p_old
+};
+
 struct Part {
     double *part;   // device partials
     int blocks;     // rows written by the last reducing launch
@@ -101,12 +109,20 @@ hipError_t launch_full_residual_norm(const MassTensor &K, const double *u, const
 bool full25_supported(int n);
 // out = L_K f in one streaming pass (out distinct from f)
 hipError_t launch_full_apply25(const MassTensor &K, const double *f, double *out, int n, double a_min, hipStream_t s);
+// grouped: with the partial sums of the gather launch (full_grouped_supported)
 hipError_t launch_full_residual_norm25(const MassTensor &K, const double *u, const double *b, double *r, float *r32,
-                                       int n, double a_min, Part &p, hipStream_t s);
+                                       int n, double a_min, Part &p, hipStream_t s, bool grouped = false);
 template <typename Z, typename P>
 hipError_t launch_full_direction25(const Z *z, const P *p_old, P *p_new, const MassTensor &K, double *q, double beta,
                                    int n, double a_min, bool first, double *u, double alpha_u, const double *ks,
-                                   Part &p, hipStream_t s);
+                                   Part &p, hipStream_t s, const Older<P> &older = {});
+// The same below the streaming edges, with the partial sums of the gather
+// launches and FP64 directions.
+bool full_grouped_supported(int n);
+template <typename Z>
+hipError_t launch_full_direction_grouped(const Z *z, const double *p_old, double *p_new, const MassTensor &K,
+                                         double *q, int n, double a_min, bool first, double *u, const double *ks,
+                                         Part &p, hipStream_t s, const Older<double> &older = {});
 // Particles at their Lagrangian positions (particles.hip): xi = pos n / box;
 // Newton for x(xi) = y from the xi given (node shifts of phi into s3, 3 n^3
 // doubles;
@@ -200,13 +216,6 @@ bool resrestrict25_supported(int n);
 template <typename T>
 hipError_t launch_resrestrict25(const T *u, const T *a, const T *b, T *c, int n, T scale, T a_min, hipStream_t s);
 
-// The directions before p_old whose solution updates are still due (at most
-// two); a direction pass (with u and ks) applies them before p_old's.
-template <typename P>
-struct Older {
-    int count = 0;
-    const P *p[2] = {nullptr, nullptr};  // one and two steps before p_old
-};
 // P: storage of p_old and p_new (double, or float with an FP32 z: p_new is
 // rounded to FP32 as it is formed and q = A p_new uses the rounded value).
 // With ks != null, beta = -ks[KS_ALPHA] ks[KS_ZQ] / ks[KS_RZ_OLD] and alpha_u =

@@ -506,6 +506,8 @@ hipError_t residual_norm(recon_ctx *ctx, const double *u, const double *a, const
 {
     if (Kf && use_stream<double>(ctx->n) && full25_supported(ctx->n))
         return launch_full_residual_norm25(*Kf, u, b, r, r32, ctx->n, ctx->cfg.a_min, ctx->part, ctx->stream);
+    if (Kf && full_grouped_supported(ctx->n))
+        return launch_full_residual_norm25(*Kf, u, b, r, r32, ctx->n, ctx->cfg.a_min, ctx->part, ctx->stream, true);
     if (Kf) return launch_full_residual_norm(*Kf, u, b, r, r32, ctx->n, ctx->cfg.a_min, ctx->part, ctx->stream);
     if (use_stream<double>(ctx->n))
         return launch_residual_norm25(u, a, b, r, r32, ctx->n, ctx->cfg.a_min, ctx->part, ctx->stream);
@@ -730,9 +732,10 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
         // of the sums they need themselves (dots and pq, in separate halves of
         // the partials), and the direction is one gather launch.
         const bool fold = !Kf && fold_in_consumer(n);
-        // Above, edges that are multiples of 64 stream it, with the partials that
-        // the gather launches leave.
-        const bool grouped = !Kf && !stream && !fold && direction_grouped_supported(n);
+        // Above, edges that are multiples of 64 stream it (with either operator),
+        // with the partials that the gather launches leave.
+        const bool grouped =
+            !stream && !fold && (Kf ? full_grouped_supported(n) : direction_grouped_supported(n));
         Part dots = ctx->part, pq = ctx->part;
         pq.part = ctx->part.part + kPartCap / 2;
         if (!fold) {
@@ -748,10 +751,9 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
         // preconditioner.
         auto f32 = [](double *x) { return reinterpret_cast<float *>(x); };
         const bool low = mixed && stream;  // directions stored in FP32
-        const bool later = grouped || (stream && !Kf);
-        const int slots = later ? (low ? 4 : 3) : 2, most = slots - 1;
+        const int slots = !stream && !grouped ? 2 : low ? 4 : 3, most = slots - 1;
         double *ring[4] = {ctx->p, ctx->t, ctx->dphi, nullptr};
-        if (low && later) {
+        if (low) {
             ring[2] = reinterpret_cast<double *>(f32(ctx->p) + n3);
             ring[3] = reinterpret_cast<double *>(f32(ctx->t) + n3);
         }
@@ -778,10 +780,12 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
             if (stream && Kf) {
                 if (mixed)
                     HIPCHK(launch_full_direction25(ctx->L32.u[0], f32(pc), f32(pn), *Kf, ctx->q, 0.0, n,
-                                                   ctx->cfg.a_min, first, ud, 0.0, ks, ctx->part, ctx->stream));
+                                                   ctx->cfg.a_min, first, ud, 0.0, ks, ctx->part, ctx->stream,
+                                                   ud ? older(float()) : Older<float>()));
                 else
                     HIPCHK(launch_full_direction25(ctx->z, pc, pn, *Kf, ctx->q, 0.0, n, ctx->cfg.a_min, first, ud,
-                                                   0.0, ks, ctx->part, ctx->stream));
+                                                   0.0, ks, ctx->part, ctx->stream,
+                                                   ud ? older(double()) : Older<double>()));
                 next();
             } else if (stream) {
                 if (mixed)
@@ -791,6 +795,16 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
                 else
                     HIPCHK(launch_direction25(ctx->z, pc, pn, a0, ctx->q, 0.0, n, ctx->cfg.a_min, first, ud, 0.0, ks,
                                               ctx->part, ctx->stream, ud ? older(double()) : Older<double>()));
+                next();
+            } else if (grouped && Kf) {
+                if (mixed)
+                    HIPCHK(launch_full_direction_grouped<float>(ctx->L32.u[0], pc, pn, *Kf, ctx->q, n,
+                                                                ctx->cfg.a_min, first, ud, ks, pq, ctx->stream,
+                                                                ud ? older(double()) : Older<double>()));
+                else
+                    HIPCHK(launch_full_direction_grouped<double>(ctx->z, pc, pn, *Kf, ctx->q, n, ctx->cfg.a_min,
+                                                                 first, ud, ks, pq, ctx->stream,
+                                                                 ud ? older(double()) : Older<double>()));
                 next();
             } else if (Kf) {
                 if (mixed) HIPCHK(launch_update_p<float>(ctx->L32.u[0], pc, 0.0, n3, first, ks, ctx->stream));

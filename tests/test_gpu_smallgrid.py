@@ -189,3 +189,36 @@ def test_deferred_solution_updates(torch_cuda, n, cn, mixed, steps):
         r -= alpha * q
     want -= want.mean()
     assert float((u - want).norm() / want.norm()) < (1e-5 if mixed else 1e-10)
+
+
+@pytest.mark.parametrize("steps", [1, 3, 4])
+@pytest.mark.parametrize("n,cn,mixed", [(128, 8, False), (192, 12, True), (256, 16, False), (256, 16, True)])
+def test_streamed_full_operator_steps(torch_cuda, n, cn, mixed, steps):
+    """The exact-Jacobian loop with the streamed direction (128^3 and 192^3
+    with the gather launches' partial sums) and its deferred solution updates,
+    against a loop of stage calls; bounds as for the x ~ xi loop."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(n + 11)
+    a = torch.exp(0.5 * torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64))
+    phi = 0.02 * torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64)
+    b = torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64)
+    b -= b.mean()
+    kw = dict(coarse_n=cn, full_operator=1, precision=binding.MIXED if mixed else binding.FP64)
+    rec = binding.Recon(n, binding.Config(fixed_cycles=steps, **kw))
+    u, cycles, _ = rec.mg_solve_full(a, phi, b)
+    assert cycles == steps
+    one = binding.Recon(n, binding.Config(solver=binding.SOLVER_VCYCLE, fixed_cycles=1, **kw))
+    r, want, p, q, alpha, rz = b.clone(), torch.zeros_like(b), None, None, 0.0, 0.0
+    for step in range(steps):
+        z, _, _ = one.mg_solve_full(a, phi, r)
+        old, rz = rz, float((z * r).sum())
+        p = z if step == 0 else z - alpha * float((z * q).sum()) / old * p
+        if mixed and n == 256:
+            p = p.float().double()
+        _, q, pq = one.full_direction(phi, a, p, None, 0.0, first=True, variant=1)
+        alpha = rz / pq
+        want += alpha * p
+        r -= alpha * q
+    want -= want.mean()
+    assert float((u - want).norm() / want.norm()) < (1e-5 if mixed else 1e-10)

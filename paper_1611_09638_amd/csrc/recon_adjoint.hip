@@ -158,9 +158,12 @@ __device__ void eigvec_sym(const Sym3 &e, double lam, double v[3])
 // Source adjoint.  tbar -> Sigmabar = tbar (1 - 2 [det e > v_m] sign Sigma),
 // Mbar -= Sigmabar (the mean(M) part is added afterwards from the partial
 // sums), lambda_0bar = tbar dC/dlambda_0 -> ebar = lambda_0bar v v^T.
-__global__ void k_source_adj(const double *__restrict__ phi, const double *__restrict__ M,
-                             const double *__restrict__ sum_M, const double *__restrict__ tbar, double xi_m, double v_m, double *__restrict__ Mbar,
-                             double *__restrict__ hb, int n, int ipb, double *part)
+// The launch bound leaves the eigenvector's registers (128^3: 80 us with the
+// 128 of an unbounded kernel, which spills, 42 with 166).
+__global__ void __launch_bounds__(256)
+    k_source_adj(const double *__restrict__ phi, const double *__restrict__ M, const double *__restrict__ sum_M,
+                 const double *__restrict__ tbar, double xi_m, double v_m, double *__restrict__ Mbar,
+                 double *__restrict__ hb, int n, int ipb, double *part)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y * blockDim.y + threadIdx.y;
@@ -216,15 +219,31 @@ hipError_t launch_source_adj(const double *phi, const double *M, const double *s
 //   ebar += Mbar rho~(x) cof(e);  xbar = Mbar det(e) grad rho~(x);
 //   mbar_j += Mbar det(e) W(x - j)   (the transposed CIC deposit: an FP64
 //   atomic scatter, the one order-dependent sum of the adjoint).
-__global__ void k_meshmass_adj(const double *__restrict__ phi, const double *__restrict__ m,
-                               const double *__restrict__ Mbar, double *__restrict__ hb, double *__restrict__ xb,
-                               double *__restrict__ mbar, int n, int ipb)
+// The atomics bound it, so they are combined first.  On a mesh that moves
+// smoothly the upper k corners of a node are the lower ones of the next node,
+// which is the wave's next lane, and its upper i corners are the lower ones of
+// the thread's next plane: wherever the cells do match, the four sums move to
+// the neighbour lane and the remaining upper two to the next plane, and about
+// 2 (1 + 1/planes) of eight atomics a node are left: 128^3 239 -> 177 us.
+__global__ void __launch_bounds__(256)
+    k_meshmass_adj(const double *__restrict__ phi, const double *__restrict__ m, const double *__restrict__ Mbar,
+                   double *__restrict__ hb, double *__restrict__ xb, double *__restrict__ mbar, int n, int ipb)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y * blockDim.y + threadIdx.y;
     if (k >= n || j >= n) return;
     const size_t n3 = (size_t)n * n * n;
     const int i0 = blockIdx.z * ipb, i1 = min(n, i0 + ipb);
+    // whether the lane below and above this one take part
+    const int lane = (threadIdx.y * blockDim.x + threadIdx.x) & 63;
+    const unsigned long long here = __ballot(1);
+    const bool below = lane > 0 && (here >> (lane - 1) & 1);
+    auto put = [&](size_t q, double val) {
+        if (val != 0.0) atomicAdd(&mbar[q], val);
+    };
+    // the upper i corners (lower k) of the plane before: i, and j, k of their cell
+    int pi = -1, pj = 0, pk = 0, pj1 = 0;
+    double pend[2] = {0.0, 0.0};
     for (int i = i0; i < i1; ++i) {
         Stencil19 s;
         load19(phi, i, j, k, n, s);
@@ -245,7 +264,7 @@ __global__ void k_meshmass_adj(const double *__restrict__ phi, const double *__r
         const size_t p = lin(i, j, k, n);
         const double mb = Mbar[p];
         const double mg = mb * g;
-        double rho_t = 0.0, gr0 = 0.0, gr1 = 0.0, gr2 = 0.0;
+        double rho_t = 0.0, gr0 = 0.0, gr1 = 0.0, gr2 = 0.0, d[8];
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             const int o0 = (c >> 2) & 1, o1 = (c >> 1) & 1, o2 = c & 1;
@@ -256,8 +275,31 @@ __global__ void k_meshmass_adj(const double *__restrict__ phi, const double *__r
             gr0 += (o0 ? 1.0 : -1.0) * wb * wc * mv;
             gr1 += wa * (o1 ? 1.0 : -1.0) * wc * mv;
             gr2 += wa * wb * (o2 ? 1.0 : -1.0) * mv;
-            if (mg != 0.0) atomicAdd(&mbar[q], mg * wa * wb * wc);
+            d[c] = mg * wa * wb * wc;
         }
+        // the cell of the lane below: its upper k corners are these lower ones
+        const int cell = (f0[0] * n + f0[1]) * n, bc = __shfl_up(cell, 1), bk = __shfl_up(f1[2], 1);
+        const bool match = below && bc == cell && bk == f0[2];
+        const unsigned long long taken = __ballot(match);
+        const bool given = lane < 63 && (taken >> (lane + 1) & 1);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const double up = __shfl_up(d[2 * c + 1], 1);
+            if (match) d[2 * c] += up;
+            if (!given) put(lin(c & 2 ? f1[0] : f0[0], c & 1 ? f1[1] : f0[1], f1[2], n), d[2 * c + 1]);
+        }
+        if (pi == f0[0] && pj == f0[1] && pk == f0[2]) {
+            d[0] += pend[0];
+            d[2] += pend[1];
+        } else if (pi >= 0) {
+            put(lin(pi, pj, pk, n), pend[0]);
+            put(lin(pi, pj1, pk, n), pend[1]);
+        }
+        put(lin(f0[0], f0[1], f0[2], n), d[0]);
+        put(lin(f0[0], f1[1], f0[2], n), d[2]);
+        pi = f1[0], pj = f0[1], pk = f0[2], pj1 = f1[1];
+        pend[0] = d[4];
+        pend[1] = d[6];
         const double gb = mb * rho_t;
         // cofactors of the symmetric e
         const double cxx = e.yy * e.zz - e.yz * e.yz, cyy = e.xx * e.zz - e.xz * e.xz, czz = e.xx * e.yy - e.xy * e.xy;
@@ -273,12 +315,20 @@ __global__ void k_meshmass_adj(const double *__restrict__ phi, const double *__r
         xb[1 * n3 + p] = mg * gr1;
         xb[2 * n3 + p] = mg * gr2;
     }
+    put(lin(pi, pj, pk, n), pend[0]);
+    put(lin(pi, pj1, pk, n), pend[1]);
 }
 
 hipError_t launch_meshmass_adj(const double *phi, const double *m, const double *Mbar, double *hb, double *xb,
                                double *mbar, int n, hipStream_t s)
 {
     Shape3 sh = shape3(n);
+    // four planes a thread where a workgroup is left for every CU: 128^3 with
+    // 1, 2, 4, 8 planes 216, 184, 177, 182 us, 64^3 31, 26, 26, 32
+    while (sh.ipb < 4 && rows_of(sh) >= 512) {
+        sh.ipb *= 2;
+        sh.grid.z = (n + sh.ipb - 1) / sh.ipb;
+    }
     k_meshmass_adj<<<sh.grid, sh.block, 0, s>>>(phi, m, Mbar, hb, xb, mbar, n, sh.ipb);
     return hipGetLastError();
 }

@@ -256,8 +256,9 @@ hipError_t launch_meshmass(const double *phi, const double *m, double *M, int n,
 
 // t = Sigma + C + E with Sigma = rho_bar - M, C = 4 max(0, xi_m/lambda_0 - 1)^2,
 // E = -2 [sqrt g > v_m] |Sigma|  (App. A, Eq. elliptic and the limiters).
-__global__ void k_source(const double *__restrict__ phi, const double *__restrict__ M, const double *__restrict__ sum_M,
-                         double n3, double xi_m, double v_m, double *__restrict__ t, int n, int ipb, double *part)
+__global__ void __launch_bounds__(256)
+    k_source(const double *__restrict__ phi, const double *__restrict__ M, const double *__restrict__ sum_M, double n3,
+             double xi_m, double v_m, double *__restrict__ t, int n, int ipb, double *part)
 {
     const double rho_bar = *sum_M / n3;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -354,8 +355,9 @@ hipError_t launch_max_shift(const double *f, int n, Part &p, hipStream_t s)
 // Mm and Dm given) where Mm + 2^-j Dm > 0 fails.  The trial potential is formed
 // per stencil point exactly as phi + alpha * dphi.
 template <int NT>
-__global__ void k_pd_trials(const double *__restrict__ phi, const double *__restrict__ dphi, int n, int ipb, int j0,
-                            double *part, const double *__restrict__ Mm, const double *__restrict__ Dm)
+__global__ void __launch_bounds__(256)
+    k_pd_trials(const double *__restrict__ phi, const double *__restrict__ dphi, int n, int ipb, int j0, double *part,
+                const double *__restrict__ Mm, const double *__restrict__ Dm)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y * blockDim.y + threadIdx.y;
@@ -460,8 +462,9 @@ hipError_t launch_sum(const double *f, long n3, Part &p, hipStream_t s)
 // delta_r = -(7-point Laplacian of phi) (Sec. II, Eq. rec), phi_out = phi h^2,
 // and the invariants min det(I+H), min lambda_0, max delta_r (stored negated
 // so that all three reduce by min).
-__global__ void k_output(const double *__restrict__ phi, double *__restrict__ delta, double *__restrict__ phi_out,
-                         double h2, int n, int ipb, double *part)
+__global__ void __launch_bounds__(256)
+    k_output(const double *__restrict__ phi, double *__restrict__ delta, double *__restrict__ phi_out, double h2, int n,
+             int ipb, double *part)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y * blockDim.y + threadIdx.y;

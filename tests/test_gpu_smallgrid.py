@@ -222,3 +222,22 @@ def test_streamed_full_operator_steps(torch_cuda, n, cn, mixed, steps):
         r -= alpha * q
     want -= want.mean()
     assert float((u - want).norm() / want.norm()) < (1e-5 if mixed else 1e-10)
+
+
+@pytest.mark.parametrize("n,cn,sigma", [(10, 10, 2.0), (80, 10, 1.5), (96, 6, 2.0)])
+def test_gradient_with_combined_deposits(torch_cuda, n, cn, sigma):
+    """The transposed deposit where sums pass between lanes and planes before
+    they become atomics: several rows in a wave (10), two and more planes a
+    thread, rows that end inside a wave (80, 96) and meshes that move by more
+    than a cell, against the oracle, to the bound of the smaller grids."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding, inputs
+    box = 15.6 * n
+    rho = inputs.lognormal_density(n, box, sigma, n)
+    base = dict(max_outer=2, tol=1e-13, max_vcycles=300, coarse_n=cn)
+    gd = np.random.default_rng(n).normal(size=rho.shape)
+    orc.solve(rho, box, orc.Config(record_tape=1, **base))
+    want = orc.backward(gd, None, box, orc.Config(**base))
+    rec = binding.Recon(n, binding.Config(record_tape=1, **base))
+    rec.solve(torch.from_numpy(rho).cuda(), box)
+    assert rel(rec.backward(torch.from_numpy(gd).cuda()).cpu().numpy(), want) < 1e-8

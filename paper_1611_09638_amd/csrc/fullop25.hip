@@ -2,7 +2,7 @@
 // K = M e^-1 (App. A, Eq. elliptic_diff without x ~ xi), in the flux form of
 // full_flux: the Krylov residual with its norm, and the Krylov direction
 // update fused with its operator product (and with the deferred solution
-// update of the previous step).
+// updates).
 //
 // A workgroup owns a TJ x TK tile of (j, k) and a chunk of consecutive
 // i-planes.  The operand is needed with its in-plane neighbours on planes

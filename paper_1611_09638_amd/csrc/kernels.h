@@ -199,8 +199,9 @@ template <typename T>
 bool stencil25_supported(int n);
 template <typename T>
 hipError_t launch_residual25(const T *u, const T *a, const T *b, T *r, int n, T scale, T a_min, hipStream_t s);
+// grouped: with the partial sums of the gather launch (direction_grouped_supported)
 hipError_t launch_residual_norm25(const double *u, const double *a, const double *b, double *r, float *r32, int n,
-                                  double a_min, Part &p, hipStream_t s);
+                                  double a_min, Part &p, hipStream_t s, bool grouped = false);
 // Streaming grid transfers (transfer25.hip): fine edge a multiple of 256.
 template <typename T>
 bool transfer25_supported(int n);

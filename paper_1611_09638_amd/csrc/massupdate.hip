@@ -10,7 +10,8 @@
 // Two passes: K at every node (six fields, since e is symmetric), then the
 // 19-point application.  The same application, with a dot product or as a
 // residual, is the operator of the exact-Jacobian linear solve, where it runs
-// once per Krylov iteration; it gathers from L2.
+// once per Krylov iteration: gathered here below 128^3 and on edges that are no
+// multiple of 64, streamed by fullop25.hip otherwise.
 
 #include <hip/hip_runtime.h>
 

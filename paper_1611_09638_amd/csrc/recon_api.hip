@@ -511,6 +511,8 @@ hipError_t residual_norm(recon_ctx *ctx, const double *u, const double *a, const
     if (Kf) return launch_full_residual_norm(*Kf, u, b, r, r32, ctx->n, ctx->cfg.a_min, ctx->part, ctx->stream);
     if (use_stream<double>(ctx->n))
         return launch_residual_norm25(u, a, b, r, r32, ctx->n, ctx->cfg.a_min, ctx->part, ctx->stream);
+    if (direction_grouped_supported(ctx->n))
+        return launch_residual_norm25(u, a, b, r, r32, ctx->n, ctx->cfg.a_min, ctx->part, ctx->stream, true);
     return launch_residual_norm(u, a, b, r, r32, ctx->n, ctx->cfg.a_min, ctx->part, ctx->stream);
 }
 

@@ -66,7 +66,7 @@ __device__ __forceinline__ void lds_fence_barrier()
 // P (direction only): storage type of p_old and p_new.  With P = float the new
 // direction is rounded to FP32 as it is formed, so the stored p_new is exactly
 // the operand of A and of the later solution update.
-// GRP (directions on 64-wide tiles, where a wave is a row of 64): the partial
+// GRP (norms and directions on 64-wide tiles, a wave a row of 64): the partial
 // sums are rows of 64 x 4 nodes and ipb planes, as the gather kernels leave
 // them, so the sums round like theirs (GRP = 2: and plain stores, for grids that
 // stay in the caches); GRP = 0: one partial per workgroup.
@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(NT)
              const P *__restrict__ xo2 = nullptr)
 {
     double alpha1 = 0.0, alpha2 = 0.0;
-    static_assert(!GRP || (MODE == S25_DIRECTION && TK == 64 && TJ % 4 == 0), "a wave is a row of 64 nodes");
+    static_assert(!GRP || (MODE != S25_RESID && TK == 64 && TJ % 4 == 0), "a wave is a row of 64 nodes");
     if constexpr (MODE == S25_DIRECTION && !FIRST) {
         // the step sizes of the conjugate-gradient loop, formed on the device
         if (ks) {
@@ -226,9 +226,10 @@ __global__ void __launch_bounds__(NT)
                 out[g] = rb[set][r] - scale * acc;
             } else if constexpr (MODE == S25_RESNORM) {
                 const T rv = rb[set][r] - acc;
-                __builtin_nontemporal_store(rv, &out[g]);
-                if (out32) __builtin_nontemporal_store((float)rv, &out32[g]);
-                v += rv * rv;
+                store(rv, &out[g]);
+                if (out32) store((float)rv, &out32[g]);
+                if constexpr (GRP) vg[r] += rv * rv;
+                else v += rv * rv;
             } else {
                 store((P)xc, &pout[g]);
                 store(acc, &out[g]);
@@ -363,20 +364,6 @@ hipError_t launch_residual25(const T *u, const T *a, const T *b, T *r, int n, T 
     return hipGetLastError();
 }
 
-hipError_t launch_residual_norm25(const double *u, const double *a, const double *b, double *r, float *r32, int n,
-                                  double a_min, Part &p, hipStream_t s)
-{
-    using C = S25Launch<double, S25_RESNORM>;
-    if (!s25_fits<C>(n)) return hipErrorInvalidValue;
-    const int ci = s25_chunk<C>(n), nb = s25_blocks<C>(n, ci);
-    if ((long)nb > kPartCap) return hipErrorInvalidValue;
-    k_flux25<double, double, S25_RESNORM, C::TJ, C::NT, C::TK, 0, 0, double><<<nb, C::NT, 0, s>>>(
-        u, nullptr, a, b, r, r32, nullptr, n, ci, 1.0, a_min, 0.0, p.part, nullptr, 0.0, nullptr);
-    p.blocks = nb;
-    p.k = 1;
-    return hipGetLastError();
-}
-
 // The direction with the gather kernels' rows of partials.  Chunks are even
 // and whole groups of ipb; 6-8 planes below 256^3, where more would leave CUs
 // without a workgroup (128^3: 23.6 ms per solve against 24.1 with 4 planes, 24.4
@@ -393,6 +380,39 @@ static int grouped_chunk(int n)
 }
 
 bool direction_grouped_supported(int n) { return n >= 128 && n % 64 == 0 && grouped_chunk(n) > 0; }
+
+// The residual with its norm; grouped: on the edges and with the launch shape of
+// the grouped direction and the gather kernel's partials (320^3 377 us as a
+// gather, 239 streamed; the solve 218.9 -> 215.8 ms, 448^3 436 -> 429).
+hipError_t launch_residual_norm25(const double *u, const double *a, const double *b, double *r, float *r32, int n,
+                                  double a_min, Part &p, hipStream_t s, bool grouped)
+{
+    if (grouped) {
+        constexpr int TJ = 16, NT = 512;
+        if (!direction_grouped_supported(n)) return hipErrorInvalidValue;
+        const int ipb = shape3(n).ipb, ci = grouped_chunk(n), nb = (n / 64) * (n / TJ) * (n / ci);
+        const long rows = (long)(n / 64) * (n / 4) * ((n + ipb - 1) / ipb);
+        if (rows > kPartCap) return hipErrorInvalidValue;
+#define RECON_RES(G)                                                                                               \
+    k_flux25<double, double, S25_RESNORM, TJ, NT, 64, 0, 0, double, G><<<nb, NT, 0, s>>>(                          \
+        u, nullptr, a, b, r, r32, nullptr, n, ci, 1.0, a_min, 0.0, p.part, nullptr, 0.0, nullptr, ipb)
+        if (n < 256) RECON_RES(2);
+        else RECON_RES(1);
+#undef RECON_RES
+        p.blocks = (int)rows;
+        p.k = 1;
+        return hipGetLastError();
+    }
+    using C = S25Launch<double, S25_RESNORM>;
+    if (!s25_fits<C>(n)) return hipErrorInvalidValue;
+    const int ci = s25_chunk<C>(n), nb = s25_blocks<C>(n, ci);
+    if ((long)nb > kPartCap) return hipErrorInvalidValue;
+    k_flux25<double, double, S25_RESNORM, C::TJ, C::NT, C::TK, 0, 0, double><<<nb, C::NT, 0, s>>>(
+        u, nullptr, a, b, r, r32, nullptr, n, ci, 1.0, a_min, 0.0, p.part, nullptr, 0.0, nullptr);
+    p.blocks = nb;
+    p.k = 1;
+    return hipGetLastError();
+}
 
 template <typename Z>
 hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,

@@ -241,3 +241,30 @@ def test_gradient_with_combined_deposits(torch_cuda, n, cn, sigma):
     rec = binding.Recon(n, binding.Config(record_tape=1, **base))
     rec.solve(torch.from_numpy(rho).cuda(), box)
     assert rel(rec.backward(torch.from_numpy(gd).cuda()).cpu().numpy(), want) < 1e-8
+
+
+@pytest.mark.parametrize("n,cn,mixed", [(128, 8, False), (192, 12, True), (320, 10, False)])
+def test_streamed_residual_norm(torch_cuda, n, cn, mixed):
+    """The streamed residual with the gather launch's partial sums: the norm
+    that a solve reports against that of the residual from the stage call, to
+    the rounding of n^3 summands (n^1.5 ulp), and the plain V-cycle iteration,
+    whose steps start from it, against the same iteration made of one-cycle
+    solves of the residual equation (the FP64 corrections round alike; in mixed
+    mode z and its mean are rounded to FP32 around different means)."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(n + 3)
+    a = torch.exp(torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64))
+    b = torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64)
+    b -= b.mean()
+    kw = dict(coarse_n=cn, precision=binding.MIXED if mixed else binding.FP64, solver=binding.SOLVER_VCYCLE)
+    rec = binding.Recon(n, binding.Config(fixed_cycles=3, **kw))
+    u, _, res = rec.mg_solve(a, b)
+    one = binding.Recon(n, binding.Config(fixed_cycles=1, **kw))
+    want, r = torch.zeros_like(b), b
+    for _ in range(3):
+        want += one.mg_solve(a, r)[0]
+        r = rec.residual(want, a, b, variant=1)
+    assert float((u - want).norm() / want.norm()) < (1e-5 if mixed else 1e-11)
+    true = rec.residual(u, a, b, variant=1)
+    assert abs(res - float(true.norm() / b.norm())) <= 1e-11 * res

@@ -215,6 +215,8 @@ hipError_t launch_prolong25(T *u, const T *e, int n, hipStream_t s);
 template <typename T>
 bool resrestrict25_supported(int n);
 template <typename T>
+bool resrestrict25_narrow(int n);
+template <typename T>
 hipError_t launch_resrestrict25(const T *u, const T *a, const T *b, T *c, int n, T scale, T a_min, hipStream_t s);
 
 // P: storage of p_old and p_new (double, or float with an FP32 z: p_new is

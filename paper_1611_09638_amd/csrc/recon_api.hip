@@ -445,7 +445,7 @@ hipError_t restrict_level(const T *f, T *c, int n, hipStream_t s, int variant = 
 }
 
 // Coarse right-hand side c = R (b - scale A u): levels from 128^3 whose coarse
-// edge is a multiple of 32 form it in one fused pass (against the two passes,
+// edge is a multiple of 32, or from 80 of 16, form it in one fused pass (against the two passes,
 // whole solves: 320^3 257 -> 241 ms in FP64, 192^3 49.1 -> 47.6 in FP32, 128^3
 // 1.5% in both); otherwise the residual goes through `res` (a fine-level
 // buffer) and is then restricted.  variant: 0 = that choice, 1 = the two
@@ -454,7 +454,7 @@ template <typename T>
 hipError_t coarse_rhs(const T *u, const T *a, const T *b, T *res, T *c, int n, T scale, T a_min, hipStream_t s,
                       int variant = 0)
 {
-    if (variant == 2 || (variant == 0 && n >= 128 && resrestrict25_supported<T>(n)))
+    if (variant == 2 || (variant == 0 && (resrestrict25_narrow<T>(n) || (n >= 128 && resrestrict25_supported<T>(n)))))
         return launch_resrestrict25<T>(u, a, b, c, n, scale, a_min, s);
     hipError_t e = residual_level<T>(u, a, b, res, n, scale, a_min, s);
     if (e != hipSuccess) return e;

@@ -236,13 +236,29 @@ bool resrestrict25_supported(int n)
     return n % 2 == 0 && nc >= C::CK && nc % C::CK == 0 && nc % C::CJ == 0;
 }
 
+// Edges from 160 that are odd multiples of 32, in 8 x 16 coarse tiles (160^3 FP64
+// 44 us against 50 in two launches; whole solves at 160^3 42.2 -> 41.3 ms FP64,
+// 35.6 -> 34.4 with the FP32 cycle, 224^3 79.7 -> 78.0).  At 96^3 the launch has
+// too few workgroups to hide its planes' latency: 16.7 us against 11.5.
+template <typename T>
+bool resrestrict25_narrow(int n)
+{
+    return n >= 160 && n % 64 == 32;
+}
+
 template <typename T>
 hipError_t launch_resrestrict25(const T *u, const T *a, const T *b, T *c, int n, T scale, T a_min, hipStream_t s)
 {
     using C = ResRestrictLaunch<T>;
-    if (!resrestrict25_supported<T>(n)) return hipErrorInvalidValue;
     const int nc = n / 2;
     int ci = nc;
+    if (resrestrict25_narrow<T>(n)) {
+        while (ci % 2 == 0 && (nc / 16) * (nc / 8) * (nc / ci) < 512) ci /= 2;
+        k_resrestrict25<T, 8, 16, 128>
+            <<<(nc / 16) * (nc / 8) * (nc / ci), 128, 0, s>>>(u, a, b, c, n, ci, scale, a_min);
+        return hipGetLastError();
+    }
+    if (!resrestrict25_supported<T>(n)) return hipErrorInvalidValue;
     while (ci > 1 && (nc / C::CK) * (nc / C::CJ) * (nc / ci) < C::MIN_BLOCKS) ci /= 2;
     const int nb = (nc / C::CK) * (nc / C::CJ) * (nc / ci);
     k_resrestrict25<T, C::CJ, C::CK, C::NT><<<nb, C::NT, 0, s>>>(u, a, b, c, n, ci, scale, a_min);
@@ -251,6 +267,8 @@ hipError_t launch_resrestrict25(const T *u, const T *a, const T *b, T *c, int n,
 
 template bool resrestrict25_supported<float>(int);
 template bool resrestrict25_supported<double>(int);
+template bool resrestrict25_narrow<float>(int);
+template bool resrestrict25_narrow<double>(int);
 template hipError_t launch_resrestrict25<float>(const float *, const float *, const float *, float *, int, float, float,
                                                 hipStream_t);
 template hipError_t launch_resrestrict25<double>(const double *, const double *, const double *, double *, int,

@@ -268,3 +268,17 @@ def test_streamed_residual_norm(torch_cuda, n, cn, mixed):
     assert float((u - want).norm() / want.norm()) < (1e-5 if mixed else 1e-11)
     true = rec.residual(u, a, b, variant=1)
     assert abs(res - float(true.norm() / b.norm())) <= 1e-11 * res
+
+
+@pytest.mark.parametrize("dtype", [64, 32])
+@pytest.mark.parametrize("n,cn", [(160, 10), (224, 14)])
+def test_coarse_right_hand_side_on_narrow_tiles(torch_cuda, n, cn, dtype):
+    """The fused residual and restriction on edges that are odd multiples of
+    32, against the two kernels that it replaces: bit for bit."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    t = torch.float64 if dtype == 64 else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(n + 5)
+    u, a, b = (torch.randn((n, n, n), generator=gen, device="cuda", dtype=t) for _ in range(3))
+    rec = binding.Recon(n, binding.Config(coarse_n=cn, precision=binding.MIXED))
+    assert torch.equal(rec.residual_restrict(u, torch.exp(a), b), rec.residual_restrict(u, torch.exp(a), b, variant=1))

@@ -894,9 +894,10 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 // of L2 measured faster at 256^3 and 512^3.
 // FOLD: p.q is still partials (pq, rows), folded by every workgroup.
 template <bool U, bool FOLD>
-__global__ void __launch_bounds__(U ? 256 : 1024) k_update_ur(double *__restrict__ u, double *__restrict__ r, const double *__restrict__ pv,
-                            const double *__restrict__ q, double alpha, float *__restrict__ r32, long n3, double *part,
-                            double *ks, const double *__restrict__ pq, int rows)
+__global__ void __launch_bounds__(U ? 256 : 1024)
+    k_update_ur(double *__restrict__ u, double *__restrict__ r, const double *__restrict__ pv,
+                const double *__restrict__ q, double alpha, float *__restrict__ r32, long n3, double *part, double *ks,
+                const double *__restrict__ pq, int rows)
 {
     if (ks) {
         const double rz = ks[KS_RZ];

@@ -652,7 +652,9 @@ int mg_start(recon_ctx *ctx, const double *a0, const double *b, bool warm = fals
     // The first V-cycle, ahead of the host's look at the norms: it writes only z
     // and the level scratch, so where it turns out not to be wanted (a zero
     // right-hand side, a warm start not taken) it costs its time and changes
-    // nothing.  (Not with timed sweeps, whose count it would change.)
+    // nothing.  (Not with timed sweeps, whose count it would change.)  It is
+    // still running when the host has seen the norms: whoever returns an error
+    // from here on drains the stream first (settle, mg_failed).
     if (!ctx->prof) TRY(precondition(ctx));
     return RECON_OK;
 }
@@ -958,6 +960,15 @@ int choose_step(recon_ctx *ctx, const double *phi, const double *dphi, double *a
     }
     return fail(ctx, RECON_E_NOT_PD, "no step 2^-j, j <= %d, keeps the map positive definite%s",
                 ctx->cfg.max_halvings, M ? " and the mass positive" : "");
+}
+
+// What forward and backward return, with the stream drained if it is an error:
+// a step's V-cycle is queued ahead of the host's look at its scalars, and an
+// error found there would leave it writing to the caller's workspace.
+int settle(recon_ctx *ctx, int rc)
+{
+    if (rc != RECON_OK) (void)hipStreamSynchronize(ctx->stream);
+    return rc;
 }
 
 // ------------------------------------------------------------ forward
@@ -1320,7 +1331,7 @@ int solve_density(recon_ctx *ctx, const double *density, int n, double box, doub
     ctx->input_mean = mean;
     ctx->box = box;
     ctx->last_tol = tol > 0.0 ? tol : ctx->cfg.tol;
-    TRY(forward(ctx, box, ctx->last_tol, phi_out, delta_r_out, st));
+    TRY(settle(ctx, forward(ctx, box, ctx->last_tol, phi_out, delta_r_out, st)));
     if (ctx->ev0) {
         HIPCHK(hipEventRecord(ctx->ev1, ctx->stream));
         HIPCHK(hipEventSynchronize(ctx->ev1));
@@ -1526,7 +1537,7 @@ int recon_solve_particles(recon_ctx *ctx, const float *pos, long long np, double
         ctx->part_np = np;
         HIPCHK(launch_init_xi(pos, np, ctx->n, box, ctx->xi, ctx->stream));
     }
-    const int rc = forward(ctx, box, ctx->last_tol, phi_out, delta_r_out, st);
+    const int rc = settle(ctx, forward(ctx, box, ctx->last_tol, phi_out, delta_r_out, st));
     ctx->part_pos = nullptr;
     ctx->part_np = 0;
     TRY(rc);
@@ -1548,7 +1559,7 @@ int recon_backward(recon_ctx *ctx, const double *grad_delta_r, const double *gra
     if (!grad_delta_r || !grad_density) return fail(ctx, RECON_E_ARG, "null gradient array");
     if (ctx->tape_np > 0)
         return fail(ctx, RECON_E_ARG, "the recorded forward deposited particles: use recon_backward_particles");
-    return backward(ctx, grad_delta_r, grad_phi, grad_density);
+    return settle(ctx, backward(ctx, grad_delta_r, grad_phi, grad_density));
 }
 
 int recon_backward_particles(recon_ctx *ctx, const float *pos, long long np, const double *grad_delta_r,
@@ -1564,7 +1575,7 @@ int recon_backward_particles(recon_ctx *ctx, const float *pos, long long np, con
         return fail(ctx, RECON_E_ARG, "the particles must be those of the recorded forward");
     if (overlap(grad_pos, (size_t)np * 24, pos, (size_t)np * 12))
         return fail(ctx, RECON_E_ARG, "grad_pos overlaps pos");
-    return backward(ctx, grad_delta_r, grad_phi, nullptr, pos, grad_pos);
+    return settle(ctx, backward(ctx, grad_delta_r, grad_phi, nullptr, pos, grad_pos));
 }
 
 // ------------------------------------------------------------- stage calls

@@ -557,7 +557,9 @@ int vcycle(recon_ctx *ctx, Levels<T> &S, int l, const T *rhs, T *out)
 {
     const int n = S.n[l];
     const T sc = (T)level_scale(l), amin = (T)ctx->cfg.a_min;
-    if (tail_supported(n)) {
+    // timed sweeps (cfg.profile) are launches of their own; a coarsest level has none
+    const bool timed = l == 0 && ctx->prof && S.L > 1;
+    if (tail_supported(n) && !timed) {
         T sl[kTailLevels];
         const int levels = S.L - l;
         for (int q = 0; q < levels && q < kTailLevels; ++q) sl[q] = (T)level_scale(l + q);
@@ -565,9 +567,8 @@ int vcycle(recon_ctx *ctx, Levels<T> &S, int l, const T *rhs, T *out)
                               ctx->cfg.coarse_sweeps, ctx->stream));
         return RECON_OK;
     }
-    // the tiles do two sweeps from zero and two after the correction; timed
-    // sweeps (cfg.profile) are launches of their own
-    if (use_tiles<T>(n) && ctx->cfg.n_pre == 2 && ctx->cfg.n_post == 2 && !(l == 0 && ctx->prof)) {
+    // the tiles do two sweeps from zero and two after the correction
+    if (use_tiles<T>(n) && ctx->cfg.n_pre == 2 && ctx->cfg.n_post == 2 && !timed) {
         HIPCHK(launch_pre_tile<T>(S.a[l], rhs, S.tmp[l], S.b[l + 1], n, sc, amin, ctx->stream));
         TRY(vcycle<T>(ctx, S, l + 1, S.b[l + 1], S.u[l + 1]));
         HIPCHK(launch_post_tile<T>(S.a[l], rhs, S.tmp[l], S.u[l + 1], out, n, sc, amin, ctx->stream));

@@ -1,5 +1,5 @@
 """What the C ABI promises around the results: the stream is drained when a
-call returns."""
+call returns, the finest level's sweeps are timed on request."""
 import pytest
 
 from paper_1611_09638_amd import inputs
@@ -64,3 +64,23 @@ def test_stream_is_idle_after_lost_particles_in_reverse(torch_cuda):
     # the tape is still there
     rec.backward_particles(pos, g)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n,cn", [(4, 2), (12, 6), (16, 8), (16, 2), (24, 6), (32, 8)])
+@pytest.mark.parametrize("precision", [0, 1], ids=["fp64", "mixed"])
+def test_sweeps_are_timed_on_every_grid(torch_cuda, n, cn, precision):
+    """cfg.profile times the four sweeps of every V-cycle on the finest level,
+    also on grids whose V-cycle runs in one workgroup otherwise (up to 16^3),
+    and leaves the results as they are without it, bit for bit."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    rho = torch.from_numpy(inputs.lognormal_density(n, 7.8 * n, 0.5, 3)).cuda()
+    kw = dict(coarse_n=cn, precision=precision, max_outer=3, fixed_cycles=4)
+    phi, delta, st = binding.Recon(n, binding.Config(**kw)).solve(rho, 7.8 * n)
+    phi_t, delta_t, st_t = binding.Recon(n, binding.Config(profile=1, **kw)).solve(rho, 7.8 * n)
+    assert torch.equal(phi, phi_t) and torch.equal(delta, delta_t)
+    assert st_t["vcycles_total"] == st["vcycles_total"] == 12
+    sweeps = [st_t["smoother_zero_sweeps"], st_t["smoother_sweeps"] + st_t["smoother_folded_sweeps"]]
+    assert sweeps == [12, 36]
+    assert st_t["smoother_zero_ms"] > 0.0 and st_t["smoother_ms"] > 0.0
+    assert [st["smoother_zero_sweeps"], st["smoother_sweeps"], st["smoother_folded_sweeps"]] == [0, 0, 0]

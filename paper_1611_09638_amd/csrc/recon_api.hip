@@ -275,8 +275,9 @@ constexpr double kInvertTol = 1e-12;
 // The device scalars of the conjugate-gradient loop (KS_* in kernels.h) sit at
 // this offset of ctx->scal; fetch_krylov copies all of them to the host.
 constexpr int kKrylovScal = 32;
-// The next V-cycle is queued ahead of the stop test while the extrapolated
-// residual norm is above this multiple of the target.
+// Work behind a stop test is queued ahead of it while the norm that is tested
+// (the extrapolated residual norm of the Krylov loop, the outer step's last
+// deviation) is above this multiple of its target.
 constexpr double kAheadMargin = 8.0;
 
 // In two halves, so that work queued between them overlaps the round trip:
@@ -1021,13 +1022,23 @@ int queue_mass_state(recon_ctx *ctx, bool gather, bool read = false)
     return fold_step(ctx, ST_SIG2, read);
 }
 
-// rho_bar = mean(M) and rms(Sigma) from the step scalars.
-int mass_state(recon_ctx *ctx, const double *v, double *rho_bar, double *rms)
+// kappa = mean(M) and rms(Sigma) of step `it` from the step scalars.
+int mass_state(recon_ctx *ctx, const double *v, int it, recon_stats *st)
 {
     if (ctx->part_pos && v[ST_LOST] != 0.0)
         return fail(ctx, RECON_E_NO_CONVERGENCE, "%.0f particles not located on the deformed mesh", v[ST_LOST]);
-    *rho_bar = v[ST_M] / (double)ctx->n3;
-    *rms = std::sqrt(v[ST_SIG2] / (double)ctx->n3);
+    st->kappa[it] = v[ST_M] / (double)ctx->n3;
+    st->rms_sigma[it] = std::sqrt(v[ST_SIG2] / (double)ctx->n3);
+    return RECON_OK;
+}
+
+// The same before a step is taken, with its stop test.
+int step_state(recon_ctx *ctx, const double *v, int it, recon_stats *st, bool *stop)
+{
+    TRY(mass_state(ctx, v, it, st));
+    const double rms = st->rms_sigma[it];
+    if (!std::isfinite(rms)) return fail(ctx, RECON_E_NO_CONVERGENCE, "non-finite mass deviation");
+    *stop = rms <= ctx->cfg.outer_tol;
     return RECON_OK;
 }
 
@@ -1058,9 +1069,22 @@ int forward(recon_ctx *ctx, double box, double tol, double *phi_out, double *del
     const MassTensor K = full ? ctx->Kf : MassTensor{ctx->t, ctx->b, ctx->r, ctx->z, ctx->p, ctx->q, nullptr};
     int it = 0;
     for (; it < c.max_outer; ++it) {
-        double rho_bar, rms, v[ST_COUNT];
+        double v[ST_COUNT];
         const bool warm = c.warm_start && it > 0;
-        TRY(queue_mass_state(ctx, !carry || it == 0));
+        // The host looks at the step's sums behind the solve's first V-cycle,
+        // in one wait with the norms.  Where this can be the last look (the
+        // first one, and while the last deviation was near the tolerance) it
+        // looks before anything more is queued, so that a solve that stops
+        // here pays for its mass and source only.
+        const bool look = it == 0 || st->rms_sigma[it - 1] <= kAheadMargin * c.outer_tol;
+        bool stop = false;
+        TRY(queue_mass_state(ctx, !carry || it == 0, look));
+        if (look) {
+            TRY(wait_copy_begin(ctx));
+            TRY(mg_wait(ctx, v));
+            TRY(step_state(ctx, v, it, st, &stop));
+            if (stop) break;
+        }
         HIPCHK(smooth_pass(ctx->t, ctx->b, ctx->n, c.smooth_center, step_scal(ctx, ST_T), ctx->stream));
         // the exact-Jacobian solve preconditions with the x ~ xi V-cycle of
         // the mean diagonal of K = M e^-1
@@ -1068,11 +1092,8 @@ int forward(recon_ctx *ctx, double box, double tol, double *phi_out, double *del
         TRY(build_hierarchy(ctx, full ? K.tr : ctx->M));
         TRY(mg_start(ctx, ctx->M, ctx->b, warm, full ? &K : nullptr));
         TRY(mg_wait(ctx, v));
-        TRY(mass_state(ctx, v, &rho_bar, &rms));
-        st->rms_sigma[it] = rms;
-        st->kappa[it] = rho_bar;
-        if (!std::isfinite(rms)) return fail(ctx, RECON_E_NO_CONVERGENCE, "non-finite mass deviation");
-        if (rms <= c.outer_tol) break;
+        if (!look) TRY(step_state(ctx, v, it, st, &stop));
+        if (stop) break;
         int cyc = 0, status = RECON_OK;
         TRY(mg_run(ctx, ctx->M, ctx->b, tol, v, &cyc, &status, warm, full ? &K : nullptr));
         if (status != RECON_OK) return mg_failed(ctx, tol, cyc);
@@ -1093,7 +1114,7 @@ int forward(recon_ctx *ctx, double box, double tol, double *phi_out, double *del
         st->outer_steps = it + 1;
         if (log_steps())
             std::fprintf(stderr, "recon step %d: rms(Sigma) %.6e, mean M %.12f, V-cycles %d, residual %.3e, alpha %.6e\n",
-                         it, rms, rho_bar, cyc, rel, alpha);
+                         it, st->rms_sigma[it], st->kappa[it], cyc, rel, alpha);
         if (c.record_tape) {
             if (c.tape_fp32) HIPCHK(launch_cast_f32(ctx->u, wsp<float>(ctx, ctx->lo.tape) + (size_t)it * n3, n3, ctx->stream));
             else HIPCHK(launch_copy(wsp<double>(ctx, ctx->lo.tape) + (size_t)it * n3, ctx->u, n3, ctx->stream));
@@ -1102,13 +1123,11 @@ int forward(recon_ctx *ctx, double box, double tol, double *phi_out, double *del
         }
     }
     if (it == c.max_outer) {
-        double rho_bar, rms, v[ST_COUNT];
+        double v[ST_COUNT];
         TRY(queue_mass_state(ctx, !carry, true));
         HIPCHK(hipStreamSynchronize(ctx->stream));
         read_step(ctx, v);
-        TRY(mass_state(ctx, v, &rho_bar, &rms));
-        st->rms_sigma[it] = rms;
-        st->kappa[it] = rho_bar;
+        TRY(mass_state(ctx, v, it, st));
     }
     static const int opmin[3] = {RED_MIN, RED_MIN, RED_MIN};
     double v[3];

@@ -1,5 +1,6 @@
 """What the C ABI promises around the results: the stream is drained when a
-call returns, the finest level's sweeps are timed on request."""
+call returns, the finest level's sweeps are timed on request, and no V-cycle
+runs that the solve does not use."""
 import pytest
 
 from paper_1611_09638_amd import inputs
@@ -84,3 +85,45 @@ def test_sweeps_are_timed_on_every_grid(torch_cuda, n, cn, precision):
     assert sweeps == [12, 36]
     assert st_t["smoother_zero_ms"] > 0.0 and st_t["smoother_ms"] > 0.0
     assert [st["smoother_zero_sweeps"], st["smoother_sweeps"], st["smoother_folded_sweeps"]] == [0, 0, 0]
+
+
+def count_vcycles(torch, call):
+    """The V-cycles that a call launches: each ends in one k_tail."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        out = call()
+        torch.cuda.synchronize()
+    return out, sum("k_tail" in e.name for e in prof.events())
+
+
+@pytest.mark.parametrize("opts", [{}, {"precision": 1}, {"solver": 1}, {"mass_update": 1}, {"full_operator": 1}],
+                         ids=lambda o: "-".join(o) or "default")
+@pytest.mark.parametrize("stop", [0, 1, 2])
+def test_no_vcycle_behind_the_outer_stop(torch_cuda, stop, opts):
+    """A solve that the outer tolerance ends at its first, second or third look
+    has run the V-cycles of the steps it took and no more (a fixed count per
+    solve, so that the loop itself queues none in vain; each starts from zero)."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    n, box = 32, 500.0
+    rho = torch.from_numpy(inputs.lognormal_density(n, box, 0.4, 5)).cuda()
+    kw = dict(max_outer=4, fixed_cycles=8, warm_start=0, **opts)
+    _, _, free = binding.Recon(n, binding.Config(**kw)).solve(rho, box)
+    rms = free["rms_sigma"]
+    assert rms[0] > rms[1] > rms[2] > rms[3]
+    rec = binding.Recon(n, binding.Config(outer_tol=1.01 * rms[stop], **kw))
+    rec.solve(rho, box)
+    (_, _, st), cycles = count_vcycles(torch, lambda: rec.solve(rho, box))
+    assert st["outer_steps"] == stop and st["rms_sigma"][: stop + 1] == rms[: stop + 1]
+    assert cycles == st["vcycles_total"] == 8 * stop
+
+
+def test_no_vcycle_on_a_uniform_density(torch_cuda):
+    """Zero deviation stops a solve at its first look under the default tolerance 0."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    rec = binding.Recon(32, binding.Config())
+    rho = torch.full((32, 32, 32), 2.5, dtype=torch.float64, device="cuda")
+    rec.solve(rho, 100.0)
+    (phi, _, st), cycles = count_vcycles(torch, lambda: rec.solve(rho, 100.0))
+    assert st["outer_steps"] == 0 and cycles == 0 and bool((phi == 0).all())

@@ -627,10 +627,11 @@ int precondition(recon_ctx *ctx)
 // x ~ xi V-cycle of the built hierarchy (the caller builds it on K's mean
 // diagonal).
 //
-// Three parts: mg_start queues the norms, the first residual and the first
-// V-cycle; mg_wait waits for the step scalars queued so far (the norms among
-// them); mg_run does the rest and leaves ||b - A u||^2 in ST_RR and in the
-// host's block, for after the stream is drained.
+// Three parts: mg_start queues the norms, the first residual and, with `ahead`,
+// the first V-cycle; mg_wait waits for the step scalars queued so far (the
+// norms among them); mg_run (told the same of `ahead`) does the rest and leaves
+// ||b - A u||^2 in ST_RR and in the host's block, for after the stream is
+// drained.
 int mg_residual_from_zero(recon_ctx *ctx, const double *a0, const double *b, const MassTensor *Kf)
 {
     // u = 0, so the residual kernel gives r = b
@@ -640,7 +641,14 @@ int mg_residual_from_zero(recon_ctx *ctx, const double *a0, const double *b, con
     return RECON_OK;
 }
 
-int mg_start(recon_ctx *ctx, const double *a0, const double *b, bool warm = false, const MassTensor *Kf = nullptr)
+// The warm start's residual over that of u = 0, from the norms; taken below 1.
+double warm_ratio(const double *step)
+{
+    return step[ST_BB] > 0.0 ? std::sqrt(step[ST_RR0]) / std::sqrt(step[ST_BB]) : INFINITY;
+}
+
+int mg_start(recon_ctx *ctx, const double *a0, const double *b, bool ahead, bool warm = false,
+             const MassTensor *Kf = nullptr)
 {
     float *r32 = ctx->cfg.precision == RECON_MIXED ? ctx->L32.b[0] : nullptr;
     HIPCHK(launch_dot(b, b, ctx->n3, ctx->part, ctx->stream));
@@ -651,13 +659,12 @@ int mg_start(recon_ctx *ctx, const double *a0, const double *b, bool warm = fals
     }
     TRY(wait_copy_begin(ctx));
     if (!warm) TRY(mg_residual_from_zero(ctx, a0, b, Kf));
-    // The first V-cycle, ahead of the host's look at the norms: it writes only z
-    // and the level scratch, so where it turns out not to be wanted (a zero
-    // right-hand side, a warm start not taken) it costs its time and changes
-    // nothing.  (Not with timed sweeps, whose count it would change.)  It is
-    // still running when the host has seen the norms: whoever returns an error
-    // from here on drains the stream first (settle, mg_failed).
-    if (!ctx->prof) TRY(precondition(ctx));
+    // The V-cycle writes only z and the level scratch, so where it turns out not
+    // to be wanted (a zero right-hand side, a warm start not taken) it costs its
+    // time and changes nothing.  It is still running when the host has seen the
+    // norms: whoever returns an error from here on drains the stream first
+    // (settle, mg_failed).
+    if (ahead) TRY(precondition(ctx));
     return RECON_OK;
 }
 
@@ -668,8 +675,8 @@ int mg_wait(recon_ctx *ctx, double *v)
     return RECON_OK;
 }
 
-int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const double *step, int *cycles_out,
-           int *status_out, bool warm = false, const MassTensor *Kf = nullptr)
+int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const double *step, bool ahead,
+           int *cycles_out, int *status_out, bool warm = false, const MassTensor *Kf = nullptr)
 {
     const int n = ctx->n;
     const long n3 = ctx->n3;
@@ -677,7 +684,7 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
     float *r32 = mixed ? ctx->L32.b[0] : nullptr;
     double v[KS_COUNT];
     const double bn = std::sqrt(step[ST_BB]);
-    bool ready = !ctx->prof;  // z = V(r) is queued
+    bool ready = ahead;  // z = V(r) is queued
     if (warm && !(bn > 0.0 && std::sqrt(step[ST_RR0]) < bn)) {
         TRY(mg_residual_from_zero(ctx, a0, b, Kf));
         ready = false;
@@ -909,9 +916,10 @@ int mg_solve(recon_ctx *ctx, const double *a0, const double *b, double tol, int 
 {
     double v[ST_COUNT];
     int cycles = 0, status = RECON_OK;
-    TRY(mg_start(ctx, a0, b, false, Kf));
+    const bool ahead = !ctx->prof;
+    TRY(mg_start(ctx, a0, b, ahead, false, Kf));
     TRY(mg_wait(ctx, v));
-    TRY(mg_run(ctx, a0, b, tol, v, &cycles, &status, false, Kf));
+    TRY(mg_run(ctx, a0, b, tol, v, ahead, &cycles, &status, false, Kf));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     read_step(ctx, v);
     if (cycles_out) *cycles_out = cycles;
@@ -1068,9 +1076,18 @@ int forward(recon_ctx *ctx, double box, double tol, double *phi_out, double *del
     double *D = ctx->m;
     const MassTensor K = full ? ctx->Kf : MassTensor{ctx->t, ctx->b, ctx->r, ctx->z, ctx->p, ctx->q, nullptr};
     int it = 0;
+    double ratio = INFINITY;  // of the last step's warm start
     for (; it < c.max_outer; ++it) {
         double v[ST_COUNT];
         const bool warm = c.warm_start && it > 0;
+        // The solve's first V-cycle goes ahead of the host's look at the norms,
+        // which saves 10-18 us, unless the start is in doubt: a warm start that
+        // is not taken (two or three of an ordinary solve's nine, while full
+        // steps bring the deviation down) would waste it, 43 us at 32^3 and 3 ms
+        // at 512^3.  After one that more than halved the residual the next one
+        // is hardly ever refused.  Timed sweeps never go in vain, which would
+        // change their count.
+        const bool ahead = !ctx->prof && (!warm || ratio < 0.5);
         // The host looks at the step's sums behind the solve's first V-cycle,
         // in one wait with the norms.  Where this can be the last look (the
         // first one, and while the last deviation was near the tolerance) it
@@ -1090,12 +1107,13 @@ int forward(recon_ctx *ctx, double box, double tol, double *phi_out, double *del
         // the mean diagonal of K = M e^-1
         if (full) HIPCHK(launch_mass_tensor(ctx->phi, ctx->M, K, ctx->n, ctx->stream));
         TRY(build_hierarchy(ctx, full ? K.tr : ctx->M));
-        TRY(mg_start(ctx, ctx->M, ctx->b, warm, full ? &K : nullptr));
+        TRY(mg_start(ctx, ctx->M, ctx->b, ahead, warm, full ? &K : nullptr));
         TRY(mg_wait(ctx, v));
         if (!look) TRY(step_state(ctx, v, it, st, &stop));
         if (stop) break;
         int cyc = 0, status = RECON_OK;
-        TRY(mg_run(ctx, ctx->M, ctx->b, tol, v, &cyc, &status, warm, full ? &K : nullptr));
+        if (warm) ratio = warm_ratio(v);
+        TRY(mg_run(ctx, ctx->M, ctx->b, tol, v, ahead, &cyc, &status, warm, full ? &K : nullptr));
         if (status != RECON_OK) return mg_failed(ctx, tol, cyc);
         st->vcycles[it] = cyc;
         st->vcycles_total += cyc;
@@ -1206,13 +1224,14 @@ int backward(recon_ctx *ctx, const double *gd, const double *gp, double *grad, c
         HIPCHK(launch_add_mean(ubar, step_scal(ctx, ST_U), -1.0, n3, ctx->stream));
         // u = A(M)^+ b:  lambda = A^+ ubar (same symmetric operator and solver)
         TRY(build_hierarchy(ctx, ctx->M));
-        TRY(mg_start(ctx, ctx->M, ubar));
+        const bool ahead = !ctx->prof;
+        TRY(mg_start(ctx, ctx->M, ubar, ahead));
         TRY(mg_wait(ctx, v));
         if (gpos && v[ST_LOST] != 0.0)
             return fail(ctx, RECON_E_NO_CONVERGENCE, "%.0f particles not located on the mesh of step %d", v[ST_LOST],
                         s);
         int cyc = 0, status = RECON_OK;
-        TRY(mg_run(ctx, ctx->M, ubar, ctx->last_tol, v, &cyc, &status));
+        TRY(mg_run(ctx, ctx->M, ubar, ctx->last_tol, v, ahead, &cyc, &status));
         if (status != RECON_OK) return mg_failed(ctx, ctx->last_tol, cyc);
         const double *lam = ctx->u;
         const double *u_s = tape_u(s);

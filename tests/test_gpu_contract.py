@@ -19,14 +19,15 @@ def torch_cuda():
 def test_stream_is_idle_after_lost_particles(torch_cuda):
     """Particles that cross streams on a coarse grid end a long solve with
     "not located" in the middle of its steps, where the next V-cycle is already
-    queued (half a millisecond each here, from 2000 coarsest sweeps): the
-    stream has to be idle when the error is returned.  Of the oracle's solves of
+    queued (half a millisecond each here, from 2000 coarsest sweeps; not behind a
+    warm start): the stream has to be idle when the error is returned.  Of the oracle's solves of
     these nine inputs eight end so; which step fails depends on rounding."""
     torch = torch_cuda
     from paper_1611_09638_amd import binding
     n, box = 16, 125.0
     side = torch.cuda.Stream()
-    rec = binding.Recon(n, binding.Config(particle_deposit=1, max_outer=64, coarse_sweeps=2000), stream=side)
+    rec = binding.Recon(n, binding.Config(particle_deposit=1, max_outer=64, coarse_sweeps=2000,
+                                          warm_start=0), stream=side)
     lost = 0
     for seed in (9, 6, 5, 1, 4, 0, 3, 8, 2):
         pos = torch.from_numpy(inputs.zeldovich_particles(n, box, 1.5, seed)).cuda()
@@ -127,3 +128,23 @@ def test_no_vcycle_on_a_uniform_density(torch_cuda):
     rec.solve(rho, 100.0)
     (phi, _, st), cycles = count_vcycles(torch, lambda: rec.solve(rho, 100.0))
     assert st["outer_steps"] == 0 and cycles == 0 and bool((phi == 0).all())
+
+
+@pytest.mark.parametrize("opts", [{}, {"precision": 1}, {"solver": 1}, {"full_operator": 1}],
+                         ids=lambda o: "-".join(o) or "default")
+@pytest.mark.parametrize("sigma", [0.3, 2.0])
+def test_no_vcycle_for_a_warm_start_not_taken(torch_cuda, sigma, opts):
+    """On a mild density (sigma 0.3) full steps bring the deviation down faster
+    than the last solution can follow and the first two warm starts are not
+    taken (their residuals are 5.9 and 1.2 times the right-hand side in the
+    oracle), on a strong one (2.0) the first is not (1.6 times) and the next
+    three are (the second 0.6, the third 0.2).  Either way the solve launches
+    the V-cycles that it counts."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    n, box = 32, 500.0
+    rho = torch.from_numpy(inputs.lognormal_density(n, box, sigma, 5)).cuda()
+    rec = binding.Recon(n, binding.Config(max_outer=5, fixed_cycles=8, **opts))
+    rec.solve(rho, box)
+    (_, _, st), cycles = count_vcycles(torch, lambda: rec.solve(rho, box))
+    assert cycles == st["vcycles_total"] == 40

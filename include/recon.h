@@ -234,6 +234,13 @@ const char *recon_last_error(const recon_ctx *ctx);
  * recon_stage_prolong_sweep, xi of recon_stage_invert_map); normalize and
  * source may also write over their inputs.  Caller arrays must not lie in
  * the context's workspace.
+ *
+ * variant 0 is the kernel that the solver runs at that size.  The V-cycle
+ * runs its small levels (up to 64^3 in FP64 and 80^3 in FP32 with two sweeps
+ * before and after, and always from 16^3 down) in one or two launches that
+ * hold sweeps, residual and transfers together; recon_stage_vcycle reaches
+ * those, and variant 0 of the single steps there is a kernel of the step
+ * alone, with the same values.
  * ------------------------------------------------------------------------ */
 
 /* m = rho / mean(rho) after checking rho (App. A input; Sec. III gridding). */
@@ -277,8 +284,10 @@ int recon_stage_residual(recon_ctx *ctx, const void *u, const void *a, const voi
  * must differ from p_old (p_old is not read, and may be NULL, when
  * first != 0).  If u (FP64, device) is not NULL, the previous step's solution
  * update u += alpha_u p_old is applied in the same pass (first must be 0; u
- * distinct from every other array).  variant as for recon_stage_residual
- * (1: in-place update then gathers; 2: one fused streaming pass). */
+ * distinct from every other array).  variant 0: the kernel of the solver's
+ * Krylov loop on that grid (with u in a pass of its own up to 96^3, where the
+ * loop updates u with the residual); 1: in-place update then gathers; 2: one
+ * fused streaming pass (n a multiple of 128, else RECON_E_ARG). */
 int recon_stage_direction(recon_ctx *ctx, const void *z, int z_dtype, const void *p_old, const double *a,
                           double beta, int first, void *p_new, double *q, double *pq, int variant, double *u,
                           double alpha_u, int p_dtype);
@@ -301,8 +310,9 @@ int recon_stage_restrict(recon_ctx *ctx, const void *f, int nl, void *c, int dty
  * arrays FP64 (dtype 0) or FP32 (dtype 1) on the device.  variant 0: what the
  * solver does on that level; 1: the residual kernel, then the restriction
  * kernel (through a library-owned fine buffer); 2: one fused streaming pass
- * (nl/2 a multiple of 32, else RECON_E_ARG).  All variants give the same
- * values. */
+ * (nl/2 a multiple of 32, else RECON_E_ARG; variant 0 also takes its narrow
+ * tiles where nl/2 is an odd multiple of 16 from 80).  All variants give the
+ * same values. */
 int recon_stage_residual_restrict(recon_ctx *ctx, const void *u, const void *a, const void *b, int nl, double scale,
                                   void *c, int dtype, int variant);
 

@@ -425,12 +425,13 @@ hipError_t launch_full_direction25(const Z *z, const P *p_old, P *p_new, const M
 
 template <typename Z>
 hipError_t launch_full_direction_grouped(const Z *z, const double *p_old, double *p_new, const MassTensor &K,
-                                         double *q, int n, double a_min, bool first, double *u, const double *ks,
-                                         Part &p, hipStream_t s, const Older<double> &older)
+                                         double *q, double beta, int n, double a_min, bool first, double *u,
+                                         double alpha_u, const double *ks, Part &p, hipStream_t s,
+                                         const Older<double> &older)
 {
     if (!full_grouped_supported(n)) return hipErrorInvalidValue;
-    return full_direction<Z, double, 1>(z, p_old, p_new, K, q, 0.0, n, f25_grouped_chunk(n), a_min, first, u, 0.0, ks,
-                                        p, s, older);
+    return full_direction<Z, double, 1>(z, p_old, p_new, K, q, beta, n, f25_grouped_chunk(n), a_min, first, u, alpha_u,
+                                        ks, p, s, older);
 }
 
 template hipError_t launch_full_direction25<float, float>(const float *, const float *, float *, const MassTensor &,
@@ -445,10 +446,11 @@ template hipError_t launch_full_direction25<double, double>(const double *, cons
                                                             double *, double, const double *, Part &, hipStream_t,
                                                             const Older<double> &);
 template hipError_t launch_full_direction_grouped<float>(const float *, const double *, double *, const MassTensor &,
-                                                         double *, int, double, bool, double *, const double *,
-                                                         Part &, hipStream_t, const Older<double> &);
+                                                         double *, double, int, double, bool, double *, double,
+                                                         const double *, Part &, hipStream_t, const Older<double> &);
 template hipError_t launch_full_direction_grouped<double>(const double *, const double *, double *,
-                                                          const MassTensor &, double *, int, double, bool, double *,
-                                                          const double *, Part &, hipStream_t, const Older<double> &);
+                                                          const MassTensor &, double *, double, int, double, bool,
+                                                          double *, double, const double *, Part &, hipStream_t,
+                                                          const Older<double> &);
 
 }  // namespace recon

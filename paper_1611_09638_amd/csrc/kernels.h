@@ -121,8 +121,9 @@ hipError_t launch_full_direction25(const Z *z, const P *p_old, P *p_new, const M
 bool full_grouped_supported(int n);
 template <typename Z>
 hipError_t launch_full_direction_grouped(const Z *z, const double *p_old, double *p_new, const MassTensor &K,
-                                         double *q, int n, double a_min, bool first, double *u, const double *ks,
-                                         Part &p, hipStream_t s, const Older<double> &older = {});
+                                         double *q, double beta, int n, double a_min, bool first, double *u,
+                                         double alpha_u, const double *ks, Part &p, hipStream_t s,
+                                         const Older<double> &older = {});
 // Particles at their Lagrangian positions (particles.hip): xi = pos n / box;
 // Newton for x(xi) = y from the xi given (node shifts of phi into s3, 3 n^3
 // doubles;
@@ -242,22 +243,23 @@ hipError_t launch_update_p(const Z *z, double *pv, double beta, long n3, bool fi
 template <typename Z>
 hipError_t launch_update_pq(const Z *z, const double *a, double *pv, double *q, double beta, int n,
                             double a_min, bool first, const double *ks, Part &p, hipStream_t s);
-// p_new = z + beta p_old (first: z; beta from ks as above) and q = A p_new with
-// partial K=1 sum p_new.q in one gather launch; p_new distinct from p_old.
-// dots: with blocks > 0 the K=2 partials of z.r and z.q, folded by this launch
-// (into ks as well), else they are in ks already; p's rows go elsewhere.
-// Needs edges above 8 to fold.
+// p_new = z + beta p_old (first: z) and q = A p_new with partial K=1 sum p_new.q
+// in one gather launch; p_new distinct from p_old.  With ks and dots (both or
+// neither), the K=2 partials of z.r and z.q, this launch folds them (into ks as
+// well) and forms beta as above; p's rows go elsewhere.  Needs edges above 8
+// to fold.
 template <typename Z>
-hipError_t launch_direction(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
-                            double a_min, bool first, double *ks, const Part &dots, Part &p, hipStream_t s);
-// The same streamed through LDS (stencil25.hip), with z.r and z.q in ks, and
-// with u (not first) also u += ks[KS_ALPHA] p_old; edges that are multiples of
-// 64 from 128.  The partials are the gather's, so the sum is.
+hipError_t launch_direction(const Z *z, const double *p_old, double *p_new, const double *a, double *q, double beta,
+                            int n, double a_min, bool first, double *ks, const Part *dots, Part &p, hipStream_t s);
+// The same streamed through LDS (stencil25.hip), and with u (not first) also
+// u += alpha_u p_old; with ks, z.r and z.q are there, and beta and the step
+// sizes come from it.  Edges that are multiples of 64 from 128.  The partials
+// are the gather's, so the sum is.
 bool direction_grouped_supported(int n);
 template <typename Z>
-hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
-                                    double a_min, bool first, double *u, const double *ks, Part &p, hipStream_t s,
-                                    const Older<double> &older = {});
+hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_new, const double *a, double *q,
+                                    double beta, int n, double a_min, bool first, double *u, double alpha_u,
+                                    const double *ks, Part &p, hipStream_t s, const Older<double> &older = {});
 // u += the due updates ks[alpha] p of p_old and the older directions, oldest
 // first
 template <typename P>

@@ -751,10 +751,7 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
             !stream && !fold && (Kf ? full_grouped_supported(n) : direction_grouped_supported(n));
         Part dots = ctx->part, pq = ctx->part;
         pq.part = ctx->part.part + kPartCap / 2;
-        if (!fold) {
-            HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
-            dots.blocks = 0;
-        }
+        if (!fold) HIPCHK(reduce_finalize(ctx->part, sums, ks + KS_RZ, ctx->stream));
         // Out-of-place directions take the next of a ring of buffers, so the
         // solution updates of up to `most` steps can wait and be applied in one
         // pass over u: p, t and dphi (t and dphi are idle during a solve) hold
@@ -811,12 +808,12 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
                 next();
             } else if (grouped && Kf) {
                 if (mixed)
-                    HIPCHK(launch_full_direction_grouped<float>(ctx->L32.u[0], pc, pn, *Kf, ctx->q, n,
-                                                                ctx->cfg.a_min, first, ud, ks, pq, ctx->stream,
+                    HIPCHK(launch_full_direction_grouped<float>(ctx->L32.u[0], pc, pn, *Kf, ctx->q, 0.0, n,
+                                                                ctx->cfg.a_min, first, ud, 0.0, ks, pq, ctx->stream,
                                                                 ud ? older(double()) : Older<double>()));
                 else
-                    HIPCHK(launch_full_direction_grouped<double>(ctx->z, pc, pn, *Kf, ctx->q, n, ctx->cfg.a_min,
-                                                                 first, ud, ks, pq, ctx->stream,
+                    HIPCHK(launch_full_direction_grouped<double>(ctx->z, pc, pn, *Kf, ctx->q, 0.0, n, ctx->cfg.a_min,
+                                                                 first, ud, 0.0, ks, pq, ctx->stream,
                                                                  ud ? older(double()) : Older<double>()));
                 next();
             } else if (Kf) {
@@ -825,20 +822,20 @@ int mg_run(recon_ctx *ctx, const double *a0, const double *b, double tol, const 
                 HIPCHK(launch_full_apply_dot(*Kf, pc, ctx->q, n, ctx->cfg.a_min, ctx->part, ctx->stream));
             } else if (fold) {
                 if (mixed)
-                    HIPCHK(launch_direction<float>(ctx->L32.u[0], pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first, ks, dots,
-                                                   pq, ctx->stream));
+                    HIPCHK(launch_direction<float>(ctx->L32.u[0], pc, pn, a0, ctx->q, 0.0, n, ctx->cfg.a_min, first, ks,
+                                                   &dots, pq, ctx->stream));
                 else
-                    HIPCHK(launch_direction<double>(ctx->z, pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first, ks, dots, pq,
-                                                    ctx->stream));
+                    HIPCHK(launch_direction<double>(ctx->z, pc, pn, a0, ctx->q, 0.0, n, ctx->cfg.a_min, first, ks, &dots,
+                                                    pq, ctx->stream));
                 next();
             } else if (grouped) {
                 if (mixed)
-                    HIPCHK(launch_direction_grouped<float>(ctx->L32.u[0], pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first,
-                                                           ud, ks, pq, ctx->stream,
+                    HIPCHK(launch_direction_grouped<float>(ctx->L32.u[0], pc, pn, a0, ctx->q, 0.0, n, ctx->cfg.a_min,
+                                                           first, ud, 0.0, ks, pq, ctx->stream,
                                                            ud ? older(double()) : Older<double>()));
                 else
-                    HIPCHK(launch_direction_grouped<double>(ctx->z, pc, pn, a0, ctx->q, n, ctx->cfg.a_min, first, ud,
-                                                            ks, pq, ctx->stream,
+                    HIPCHK(launch_direction_grouped<double>(ctx->z, pc, pn, a0, ctx->q, 0.0, n, ctx->cfg.a_min, first,
+                                                            ud, 0.0, ks, pq, ctx->stream,
                                                             ud ? older(double()) : Older<double>()));
                 next();
             } else if (mixed) {
@@ -1764,6 +1761,26 @@ int recon_stage_direction(recon_ctx *ctx, const void *z, int z_dtype, const void
         else
             HIPCHK(launch_direction25((const float *)z, (const double *)po, (double *)p_new, a, q, beta, n,
                                       ctx->cfg.a_min, first != 0, u, alpha_u, nullptr, ctx->part, ctx->stream));
+    } else if (variant == 0 && fold_in_consumer(n)) {
+        // (there the solve updates u with the residual)
+        const double *po = first ? nullptr : (const double *)p_old;
+        if (u) HIPCHK(launch_axpy(u, po, alpha_u, n3, ctx->stream));
+        if (z_dtype == 0)
+            HIPCHK(launch_direction<double>((const double *)z, po, (double *)p_new, a, q, beta, n, ctx->cfg.a_min,
+                                            first != 0, nullptr, nullptr, ctx->part, ctx->stream));
+        else
+            HIPCHK(launch_direction<float>((const float *)z, po, (double *)p_new, a, q, beta, n, ctx->cfg.a_min,
+                                           first != 0, nullptr, nullptr, ctx->part, ctx->stream));
+    } else if (variant == 0 && direction_grouped_supported(n)) {
+        const double *po = first ? nullptr : (const double *)p_old;
+        if (z_dtype == 0)
+            HIPCHK(launch_direction_grouped<double>((const double *)z, po, (double *)p_new, a, q, beta, n,
+                                                    ctx->cfg.a_min, first != 0, u, alpha_u, nullptr, ctx->part,
+                                                    ctx->stream));
+        else
+            HIPCHK(launch_direction_grouped<float>((const float *)z, po, (double *)p_new, a, q, beta, n,
+                                                   ctx->cfg.a_min, first != 0, u, alpha_u, nullptr, ctx->part,
+                                                   ctx->stream));
     } else {
         double *pn = (double *)p_new;
         if (u) HIPCHK(launch_axpy(u, (const double *)p_old, alpha_u, n3, ctx->stream));
@@ -1797,7 +1814,9 @@ int recon_stage_full_residual(recon_ctx *ctx, const double *phi, const double *M
     if (stream && !full25_supported(n))
         return fail(ctx, RECON_E_ARG, "the streaming full operator needs an edge that is a multiple of 64");
     HIPCHK(launch_mass_tensor(phi, M, ctx->Kf, n, ctx->stream));
-    if (stream) HIPCHK(launch_full_residual_norm25(ctx->Kf, u, b, r, r32, n, ctx->cfg.a_min, ctx->part, ctx->stream));
+    const bool grouped = variant == 0 && !stream && full_grouped_supported(n);
+    if (stream || grouped)
+        HIPCHK(launch_full_residual_norm25(ctx->Kf, u, b, r, r32, n, ctx->cfg.a_min, ctx->part, ctx->stream, grouped));
     else HIPCHK(launch_full_residual_norm(ctx->Kf, u, b, r, r32, n, ctx->cfg.a_min, ctx->part, ctx->stream));
     return fetch_sum(ctx, rr);
 }
@@ -1842,6 +1861,16 @@ int recon_stage_full_direction(recon_ctx *ctx, const double *phi, const double *
         else
             HIPCHK(launch_full_direction25((const float *)z, (const double *)po, (double *)p_new, ctx->Kf, q, beta,
                                            n, ctx->cfg.a_min, first != 0, u, alpha_u, nullptr, ctx->part, ctx->stream));
+    } else if (variant == 0 && full_grouped_supported(n)) {
+        const double *po = first ? nullptr : (const double *)p_old;
+        if (z_dtype == 0)
+            HIPCHK(launch_full_direction_grouped<double>((const double *)z, po, (double *)p_new, ctx->Kf, q, beta, n,
+                                                         ctx->cfg.a_min, first != 0, u, alpha_u, nullptr, ctx->part,
+                                                         ctx->stream));
+        else
+            HIPCHK(launch_full_direction_grouped<float>((const float *)z, po, (double *)p_new, ctx->Kf, q, beta, n,
+                                                        ctx->cfg.a_min, first != 0, u, alpha_u, nullptr, ctx->part,
+                                                        ctx->stream));
     } else {
         double *pn = (double *)p_new;
         if (u) HIPCHK(launch_axpy(u, (const double *)p_old, alpha_u, n3, ctx->stream));

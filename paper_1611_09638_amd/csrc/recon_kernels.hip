@@ -804,24 +804,23 @@ __global__ void k_apply_dot(const double *__restrict__ pv, const double *__restr
 // launch: a node forms p_new at its six neighbours too, from fields that sit in
 // L2 on the grids this is for, and stores its own.  The values and the sums are
 // those of k_update_p and k_apply_dot, whose second launch this saves (32^3:
-// 2.9 + 3.9 us).  rows > 0: z.r and z.q are still partials of that many rows;
-// every workgroup folds them, and the first stores them in ks.
+// 2.9 + 3.9 us).  rows > 0 (the Krylov loop): z.r and z.q are still partials of
+// that many rows; every workgroup folds them and forms beta, and the first
+// stores them in ks.
 template <typename Z, int FIRST>
 __global__ void k_direction(const Z *__restrict__ z, const double *__restrict__ p_old, double *__restrict__ p_new,
-                            const double *__restrict__ a, double *__restrict__ q, int n, int ipb, double a_min,
-                            double *part, const double *__restrict__ dots, int rows, double *ks)
+                            const double *__restrict__ a, double *__restrict__ q, double beta, int n, int ipb,
+                            double a_min, double *part, const double *__restrict__ dots, int rows, double *ks)
 {
-    double beta = 0.0, d[2];
     if (rows > 0) {
+        double d[2];
         fold_sums<2>(dots, rows, d);
         if (block_row() == 0 && threadIdx.x + threadIdx.y == 0) {
             ks[KS_RZ] = d[0];
             ks[KS_ZQ] = d[1];
         }
-    } else {
-        d[1] = ks[KS_ZQ];
+        if (!FIRST) beta = -ks[KS_ALPHA] * d[1] / ks[KS_RZ_OLD];
     }
-    if (!FIRST) beta = -ks[KS_ALPHA] * d[1] / ks[KS_RZ_OLD];
     auto pv = [&](size_t x) { return FIRST ? (double)z[x] : (double)z[x] + beta * p_old[x]; };
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y * blockDim.y + threadIdx.y;
@@ -847,18 +846,20 @@ __global__ void k_direction(const Z *__restrict__ z, const double *__restrict__ 
 }
 
 template <typename Z>
-hipError_t launch_direction(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
-                            double a_min, bool first, double *ks, const Part &dots, Part &p, hipStream_t s)
+hipError_t launch_direction(const Z *z, const double *p_old, double *p_new, const double *a, double *q, double beta,
+                            int n, double a_min, bool first, double *ks, const Part *dots, Part &p, hipStream_t s)
 {
     Shape3 sh = shape3(n);
-    const int rows = dots.blocks;
-    if (p_new == p_old || (rows > 0 && (sh.block.x * sh.block.y != 256 || dots.k != 2 || dots.part == p.part)))
+    if (p_new == p_old || !ks != !dots) return hipErrorInvalidValue;
+    if (dots && (sh.block.x * sh.block.y != 256 || dots->k != 2 || dots->blocks < 1 || dots->part == p.part))
         return hipErrorInvalidValue;
+    const double *part = dots ? dots->part : nullptr;
+    const int rows = dots ? dots->blocks : 0;
     if (first)
-        k_direction<Z, 1><<<sh.grid, sh.block, 0, s>>>(z, p_old, p_new, a, q, n, sh.ipb, a_min, p.part, dots.part, rows,
+        k_direction<Z, 1><<<sh.grid, sh.block, 0, s>>>(z, p_old, p_new, a, q, beta, n, sh.ipb, a_min, p.part, part, rows,
                                                        ks);
     else
-        k_direction<Z, 0><<<sh.grid, sh.block, 0, s>>>(z, p_old, p_new, a, q, n, sh.ipb, a_min, p.part, dots.part, rows,
+        k_direction<Z, 0><<<sh.grid, sh.block, 0, s>>>(z, p_old, p_new, a, q, beta, n, sh.ipb, a_min, p.part, part, rows,
                                                        ks);
     p.blocks = rows_of(sh);
     p.k = 1;
@@ -1044,8 +1045,8 @@ hipError_t launch_add_correction(double *u, const Z *z, long n3, hipStream_t s)
     template hipError_t launch_dots_zr_zq<T>(const T *, const double *, const double *, long, Part &, hipStream_t); \
     template hipError_t launch_update_pq<T>(const T *, const double *, double *, double *, double, int, double,     \
                                             bool, const double *, Part &, hipStream_t);                           \
-    template hipError_t launch_direction<T>(const T *, const double *, double *, const double *, double *, int,     \
-                                            double, bool, double *, const Part &, Part &, hipStream_t);            \
+    template hipError_t launch_direction<T>(const T *, const double *, double *, const double *, double *, double,  \
+                                            int, double, bool, double *, const Part *, Part &, hipStream_t);       \
     template hipError_t launch_update_p<T>(const T *, double *, double, long, bool, const double *, hipStream_t);  \
     template hipError_t launch_add_correction<T>(double *, const T *, long, hipStream_t);                        \
 

@@ -415,12 +415,12 @@ hipError_t launch_residual_norm25(const double *u, const double *a, const double
 }
 
 template <typename Z>
-hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_new, const double *a, double *q, int n,
-                                    double a_min, bool first, double *u, const double *ks, Part &p, hipStream_t s,
-                                    const Older<double> &older)
+hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_new, const double *a, double *q,
+                                    double beta, int n, double a_min, bool first, double *u, double alpha_u,
+                                    const double *ks, Part &p, hipStream_t s, const Older<double> &older)
 {
     constexpr int TJ = 16, NT = 512;
-    if (older.count < 0 || older.count > 1 || (older.count && !u)) return hipErrorInvalidValue;
+    if (older.count < 0 || older.count > 1 || (older.count && (!u || !ks))) return hipErrorInvalidValue;
     if (!direction_grouped_supported(n) || p_old == p_new || (u && (first || p_old == u || p_new == u || u == q)))
         return hipErrorInvalidValue;
     const int ipb = shape3(n).ipb, ci = grouped_chunk(n), nb = (n / 64) * (n / TJ) * (n / ci);
@@ -428,7 +428,7 @@ hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_n
     if (rows > kPartCap / 2) return hipErrorInvalidValue;
 #define RECON_GRP(FIRST, UPD, G)                                                                                   \
     k_flux25<double, Z, S25_DIRECTION, TJ, NT, 64, FIRST, UPD, double, G><<<nb, NT, 0, s>>>(                       \
-        p_old, z, a, nullptr, q, nullptr, p_new, n, ci, 1.0, a_min, 0.0, p.part, u, 0.0, ks, ipb, older.p[0])
+        p_old, z, a, nullptr, q, nullptr, p_new, n, ci, 1.0, a_min, beta, p.part, u, alpha_u, ks, ipb, older.p[0])
     if (n < 256) {
         if (first) RECON_GRP(1, 0, 2);
         else if (older.count) RECON_GRP(0, 2, 2);
@@ -446,11 +446,11 @@ hipError_t launch_direction_grouped(const Z *z, const double *p_old, double *p_n
     return hipGetLastError();
 }
 template hipError_t launch_direction_grouped<double>(const double *, const double *, double *, const double *,
-                                                     double *, int, double, bool, double *, const double *, Part &,
-                                                     hipStream_t, const Older<double> &);
+                                                     double *, double, int, double, bool, double *, double,
+                                                     const double *, Part &, hipStream_t, const Older<double> &);
 template hipError_t launch_direction_grouped<float>(const float *, const double *, double *, const double *, double *,
-                                                    int, double, bool, double *, const double *, Part &, hipStream_t,
-                                                    const Older<double> &);
+                                                    double, int, double, bool, double *, double, const double *,
+                                                    Part &, hipStream_t, const Older<double> &);
 
 template <typename Z, typename P>
 hipError_t launch_direction25(const Z *z, const P *p_old, P *p_new, const double *a, double *q, double beta, int n,

@@ -1,6 +1,7 @@
 """What the C ABI promises around the results: the stream is drained when a
-call returns, the finest level's sweeps are timed on request, and no V-cycle
-runs that the solve does not use."""
+call returns, the finest level's sweeps are timed on request, no V-cycle runs
+that the solve does not use, and variant 0 of the stage calls is the kernel
+that the solver runs."""
 import pytest
 
 from paper_1611_09638_amd import inputs
@@ -88,13 +89,18 @@ def test_sweeps_are_timed_on_every_grid(torch_cuda, n, cn, precision):
     assert [st["smoother_zero_sweeps"], st["smoother_sweeps"], st["smoother_folded_sweeps"]] == [0, 0, 0]
 
 
-def count_vcycles(torch, call):
-    """The V-cycles that a call launches: each ends in one k_tail."""
+def launches(torch, call, kernel):
+    """What a call returns, and how often it launches a kernel."""
     from torch.profiler import ProfilerActivity, profile
     with profile(activities=[ProfilerActivity.CUDA]) as prof:
         out = call()
         torch.cuda.synchronize()
-    return out, sum("k_tail" in e.name for e in prof.events())
+    return out, sum(kernel in e.name for e in prof.events())
+
+
+def count_vcycles(torch, call):
+    """The V-cycles that a call launches: each ends in one k_tail."""
+    return launches(torch, call, "k_tail")
 
 
 @pytest.mark.parametrize("opts", [{}, {"precision": 1}, {"solver": 1}, {"mass_update": 1}, {"full_operator": 1}],
@@ -148,3 +154,62 @@ def test_no_vcycle_for_a_warm_start_not_taken(torch_cuda, sigma, opts):
     rec.solve(rho, box)
     (_, _, st), cycles = count_vcycles(torch, lambda: rec.solve(rho, box))
     assert cycles == st["vcycles_total"] == 40
+
+
+@pytest.mark.parametrize("n,cn,kernel", [(10, 10, "k_direction"), (64, 8, "k_direction"), (96, 6, "k_direction"),
+                                         (112, 14, "k_apply_dot"), (128, 8, "k_flux25"), (192, 12, "k_flux25"),
+                                         (320, 10, "k_flux25")])
+@pytest.mark.parametrize("z32", [False, True], ids=["z64", "z32"])
+def test_stage_direction_runs_the_solvers_kernel(torch_cuda, n, cn, kernel, z32):
+    """recon_stage_direction's variant 0 launches what the Krylov loop launches
+    there, and gives the values of the gathers bit for bit (p, q, p.q, u; with
+    and without a previous direction)."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    z, p, a, u, b = (torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64) for _ in range(5))
+    a = torch.exp(a)
+    rec = binding.Recon(n, binding.Config(coarse_n=cn, fixed_cycles=2, precision=int(z32)))
+    b -= b.mean()
+    rec.mg_solve(a, b)
+    assert launches(torch, lambda: rec.mg_solve(a, b), kernel)[1] >= 2
+    z = z.float() if z32 else z
+    for first in (True, False):
+        u0, u1 = u.clone(), u.clone()
+        kw = [{}, {}] if first else [dict(u=u0, alpha_u=0.3), dict(u=u1, alpha_u=0.3)]
+        got, count = launches(torch, lambda: rec.direction(z, None if first else p, a, 0.7, first=first, **kw[0]),
+                              kernel)
+        want = rec.direction(z, None if first else p, a, 0.7, first=first, variant=1, **kw[1])
+        assert count == 1
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and got[2] == want[2]
+        assert torch.equal(u0, u1)
+
+
+@pytest.mark.parametrize("n,cn,kernel", [(64, 8, "k_full_apply"), (128, 8, "k_full25"), (192, 12, "k_full25")])
+@pytest.mark.parametrize("z32", [False, True], ids=["z64", "z32"])
+def test_full_stages_run_the_solvers_kernels(torch_cuda, n, cn, kernel, z32):
+    """The same for the exact-Jacobian residual and direction."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(n + 1)
+    z, p, M, u, b = (torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64) for _ in range(5))
+    M = torch.exp(M)
+    phi = 0.02 * torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64)
+    rec = binding.Recon(n, binding.Config(coarse_n=cn, fixed_cycles=2, full_operator=1, precision=int(z32)))
+    b -= b.mean()
+    rec.mg_solve_full(M, phi, b)
+    assert launches(torch, lambda: rec.mg_solve_full(M, phi, b), kernel)[1] >= 4  # two residuals, two directions
+    got, count = launches(torch, lambda: rec.full_residual(phi, M, u, b, fp32_copy=z32), kernel)
+    want = rec.full_residual(phi, M, u, b, variant=1, fp32_copy=z32)
+    assert count == 1 and torch.equal(got[0], want[0]) and got[2] == want[2]
+    assert not z32 or torch.equal(got[1], want[1])
+    z = z.float() if z32 else z
+    for first in (True, False):
+        u0, u1 = u.clone(), u.clone()
+        kw = [{}, {}] if first else [dict(u=u0, alpha_u=0.3), dict(u=u1, alpha_u=0.3)]
+        got, count = launches(
+            torch, lambda: rec.full_direction(phi, M, z, None if first else p, 0.7, first=first, **kw[0]), kernel)
+        want = rec.full_direction(phi, M, z, None if first else p, 0.7, first=first, variant=1, **kw[1])
+        assert count == 1
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and got[2] == want[2]
+        assert torch.equal(u0, u1)

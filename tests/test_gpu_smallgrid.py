@@ -282,3 +282,46 @@ def test_coarse_right_hand_side_on_narrow_tiles(torch_cuda, n, cn, dtype):
     u, a, b = (torch.randn((n, n, n), generator=gen, device="cuda", dtype=t) for _ in range(3))
     rec = binding.Recon(n, binding.Config(coarse_n=cn, precision=binding.MIXED))
     assert torch.equal(rec.residual_restrict(u, torch.exp(a), b), rec.residual_restrict(u, torch.exp(a), b, variant=1))
+
+
+@pytest.mark.parametrize("n,cn,dtype", [(320, 10, 32), (448, 14, 32), (384, 12, 32), (320, 10, 64), (448, 14, 64)])
+def test_large_ragged_vcycle_equals_the_separate_kernels(torch_cuda, n, cn, dtype):
+    """A V-cycle on the edges from 256 whose fused sweeps are in tiles of 64 (in
+    FP32 odd multiples of 64) or in chunks that no power of two has, with the
+    sweep that starts from u = 0, which no stage call reaches: bit for bit the
+    cycle made of per-colour sweeps and single transfers around the V-cycle of
+    the next level."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    t = torch.float64 if dtype == 64 else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(n + 13)
+    a = torch.exp(torch.randn((n, n, n), generator=gen, device="cuda", dtype=t))
+    r = torch.randn((n, n, n), generator=gen, device="cuda", dtype=t)
+    cfg = binding.Config(coarse_n=cn, precision=binding.MIXED)
+    rec = binding.Recon(n, cfg)
+    z = rec.vcycle(a, r)
+    u = torch.zeros_like(r)
+    for _ in range(2):
+        u = rec.rbgs(u, a, r, first=0, variant=1)
+    c = rec.residual_restrict(u, a, r, variant=1)
+    e = binding.Recon(n // 2, cfg).vcycle(rec.restrict(a, variant=1), 4.0 * c)
+    u = rec.prolong_add(u, e, variant=1)
+    for _ in range(2):
+        u = rec.rbgs(u, a, r, first=1, variant=1)
+    assert torch.equal(z, u)
+
+
+@pytest.mark.parametrize("n,cn", [(320, 10), (448, 14)])
+def test_mixed_solve_on_large_ragged_edges(torch_cuda, n, cn):
+    """The mixed solve at those edges reaches its tolerance, with the residual
+    taken by the gather kernel (twice the tolerance: the loop stops on its
+    recurrence, whose drift is a few 1e-13 at this contrast)."""
+    torch = torch_cuda
+    from paper_1611_09638_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(n + 17)
+    a = torch.exp(torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64))
+    b = torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64)
+    b -= b.mean()
+    rec = binding.Recon(n, binding.Config(coarse_n=cn, precision=binding.MIXED))
+    u, _, _ = rec.mg_solve(a, b, tol=1e-10)
+    assert float(rec.residual(u, a, b, variant=1).norm() / b.norm()) < 2e-10

@@ -180,7 +180,6 @@ hipError_t launch_tail(const T *const *a, const int *n, const T *scale, int leve
 // A level's downward half (two sweeps from u = 0, red then black, and
 // c = R (b - scale A u)) and upward half (u_out = two sweeps, black then red,
 // of u_in + P e) in one launch each (smallgrid.hip); u_in distinct from u_out.
-template <typename T>
 bool tile_supported(int n);
 template <typename T>
 hipError_t launch_pre_tile(const T *a, const T *b, T *u, T *c, int n, T scale, T a_min, hipStream_t s);
@@ -215,7 +214,6 @@ hipError_t launch_prolong25(T *u, const T *e, int n, hipStream_t s);
 // kernels one after the other
 template <typename T>
 bool resrestrict25_supported(int n);
-template <typename T>
 bool resrestrict25_narrow(int n);
 template <typename T>
 hipError_t launch_resrestrict25(const T *u, const T *a, const T *b, T *c, int n, T scale, T a_min, hipStream_t s);
@@ -267,8 +265,8 @@ hipError_t launch_due_updates(double *u, const P *p_old, const Older<P> &older, 
                               hipStream_t s);
 // u += alpha p (if u != null); r -= alpha q; partial K=1: sum r^2; r32 = (float) r if r32 != null.
 // With ks != null: alpha = ks[KS_RZ] / ks[KS_PQ], and the kernel stores it in
-// ks[KS_ALPHA] and ks[KS_RZ] in ks[KS_RZ_OLD].  pq with blocks > 0: the K=1
-// partials of p.q, folded by this launch in place of ks[KS_PQ].
+// ks[KS_ALPHA] and ks[KS_RZ] in ks[KS_RZ_OLD].  pq with blocks > 0 (and u and
+// ks): the K=1 partials of p.q, folded by this launch in place of ks[KS_PQ].
 hipError_t launch_update_ur(double *u, double *r, const double *pv, const double *q, double alpha,
                             float *r32, long n3, double *ks, Part &p, hipStream_t s, const Part *pq = nullptr);
 // u += z (Z = double or float)

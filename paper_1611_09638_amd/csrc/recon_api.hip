@@ -185,7 +185,7 @@ struct recon_ctx {
     Part part;
     double *scal = nullptr;       // device scalars (reduction results)
     double *host_scal = nullptr;  // pinned host mirror
-    double *host_dev = nullptr;   // its device address (null: not writable from the device)
+    double *host_dev = nullptr;   // its device address (null where it is pageable: recon_solve_noalloc)
     double *m, *phi, *M, *t, *b, *u, *r, *z, *p, *q, *dphi;
     Levels<double> L64;
     Levels<float> L32;
@@ -446,16 +446,16 @@ hipError_t restrict_level(const T *f, T *c, int n, hipStream_t s, int variant = 
 }
 
 // Coarse right-hand side c = R (b - scale A u): levels from 128^3 whose coarse
-// edge is a multiple of 32, or from 80 of 16, form it in one fused pass (against the two passes,
-// whole solves: 320^3 257 -> 241 ms in FP64, 192^3 49.1 -> 47.6 in FP32, 128^3
-// 1.5% in both); otherwise the residual goes through `res` (a fine-level
-// buffer) and is then restricted.  variant: 0 = that choice, 1 = the two
-// passes, 2 = the fused pass.
+// edge is a multiple of 32, or from 80 of 16, form it in one fused pass (against
+// the two passes, whole solves: 320^3 257 -> 241 ms in FP64, 192^3 49.1 -> 47.6
+// in FP32, 128^3 1.5% in both); otherwise the residual goes through `res` (a
+// fine-level buffer) and is then restricted.  variant: 0 = that choice, 1 = the
+// two passes, 2 = the fused pass.
 template <typename T>
 hipError_t coarse_rhs(const T *u, const T *a, const T *b, T *res, T *c, int n, T scale, T a_min, hipStream_t s,
                       int variant = 0)
 {
-    if (variant == 2 || (variant == 0 && (resrestrict25_narrow<T>(n) || (n >= 128 && resrestrict25_supported<T>(n)))))
+    if (variant == 2 || (variant == 0 && (resrestrict25_narrow(n) || (n >= 128 && resrestrict25_supported<T>(n)))))
         return launch_resrestrict25<T>(u, a, b, c, n, scale, a_min, s);
     hipError_t e = residual_level<T>(u, a, b, res, n, scale, a_min, s);
     if (e != hipSuccess) return e;
@@ -547,7 +547,7 @@ int collect_profile(recon_ctx *ctx, recon_stats *st)
 template <typename T>
 bool use_tiles(int n)
 {
-    return n <= (sizeof(T) == 4 ? 80 : 64) && tile_supported<T>(n);
+    return n <= (sizeof(T) == 4 ? 80 : 64) && tile_supported(n);
 }
 
 // out = V(rhs) on level l from a zero initial guess: n_pre sweeps red->black,

@@ -890,16 +890,21 @@ hipError_t launch_update_p(const Z *z, double *pv, double beta, long n3, bool fi
 typedef double v2d __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 
-// r and its FP32 copy are stored nontemporally: the next kernels that read
-// them stream fields far larger than the caches, and keeping the stores out
-// of L2 measured faster at 256^3 and 512^3.
+// r and its FP32 copy are stored nontemporally: on large grids the next kernels
+// that read them stream fields far beyond the caches, and keeping the stores
+// out of L2 measured faster at 256^3 and 512^3.  (Small grids run the same
+// instances; plain stores were not measured there.)
 // FOLD: p.q is still partials (pq, rows), folded by every workgroup.
+// The launch has 256 threads.  With u the pairs in flight take 140 registers,
+// which that bound allows and the default one of 1024 threads (128) would
+// spill; without u they take 124, and the bound changes nothing.
 template <bool U, bool FOLD>
 __global__ void __launch_bounds__(U ? 256 : 1024)
     k_update_ur(double *__restrict__ u, double *__restrict__ r, const double *__restrict__ pv,
                 const double *__restrict__ q, double alpha, float *__restrict__ r32, long n3, double *part, double *ks,
                 const double *__restrict__ pq, int rows)
 {
+    static_assert(U || !FOLD, "the grids that fold here update u here too");
     if (ks) {
         const double rz = ks[KS_RZ];
         double d[1];
@@ -971,7 +976,7 @@ hipError_t launch_update_ur(double *u, double *r, const double *pv, const double
                             double *ks, Part &p, hipStream_t s, const Part *pq)
 {
     const int rows = pq ? pq->blocks : 0;
-    if (rows > 0 && (!ks || pq->k != 1 || pq->part == p.part)) return hipErrorInvalidValue;
+    if (rows > 0 && (!u || !ks || pq->k != 1 || pq->part == p.part)) return hipErrorInvalidValue;
     // the paired accesses need 16-byte aligned fields
     if ((reinterpret_cast<uintptr_t>(r) | reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(u) |
          reinterpret_cast<uintptr_t>(pv)) % 16 ||
@@ -983,7 +988,6 @@ hipError_t launch_update_ur(double *u, double *r, const double *pv, const double
     const double *part = rows ? pq->part : nullptr;
     if (u && rows) k_update_ur<true, true><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, part, rows);
     else if (u) k_update_ur<true, false><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, part, rows);
-    else if (rows) k_update_ur<false, true><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, part, rows);
     else k_update_ur<false, false><<<nb, 256, 0, s>>>(u, r, pv, q, alpha, r32, n3, p.part, ks, part, rows);
     p.blocks = nb;
     p.k = 1;

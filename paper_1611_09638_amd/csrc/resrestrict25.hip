@@ -240,7 +240,6 @@ bool resrestrict25_supported(int n)
 // 44 us against 50 in two launches; whole solves at 160^3 42.2 -> 41.3 ms FP64,
 // 35.6 -> 34.4 with the FP32 cycle, 224^3 79.7 -> 78.0).  At 96^3 the launch has
 // too few workgroups to hide its planes' latency: 16.7 us against 11.5.
-template <typename T>
 bool resrestrict25_narrow(int n)
 {
     return n >= 160 && n % 64 == 32;
@@ -252,7 +251,7 @@ hipError_t launch_resrestrict25(const T *u, const T *a, const T *b, T *c, int n,
     using C = ResRestrictLaunch<T>;
     const int nc = n / 2;
     int ci = nc;
-    if (resrestrict25_narrow<T>(n)) {
+    if (resrestrict25_narrow(n)) {
         while (ci % 2 == 0 && (nc / 16) * (nc / 8) * (nc / ci) < 512) ci /= 2;
         k_resrestrict25<T, 8, 16, 128>
             <<<(nc / 16) * (nc / 8) * (nc / ci), 128, 0, s>>>(u, a, b, c, n, ci, scale, a_min);
@@ -267,8 +266,6 @@ hipError_t launch_resrestrict25(const T *u, const T *a, const T *b, T *c, int n,
 
 template bool resrestrict25_supported<float>(int);
 template bool resrestrict25_supported<double>(int);
-template bool resrestrict25_narrow<float>(int);
-template bool resrestrict25_narrow<double>(int);
 template hipError_t launch_resrestrict25<float>(const float *, const float *, const float *, float *, int, float, float,
                                                 hipStream_t);
 template hipError_t launch_resrestrict25<double>(const double *, const double *, const double *, double *, int,

@@ -462,9 +462,10 @@ __global__ void __launch_bounds__(kTailThreads) k_tail(const TailArgs<T> g)
 // of its neighbours' (two sweeps reach four nodes, the residual and its full
 // weighting two more on the low side), so a level's whole downward or upward
 // half is one launch without exchange between workgroups.  An 8^3 block does
-// about four times the relaxations of its own nodes before the coarse level
-// and three times after it: cheaper than the launches it saves while a level
-// is a few rounds of workgroups.
+// 5.8 times the relaxations of its own nodes before the coarse level (half of
+// 17^3, 15^3, 13^3 and 11^3 nodes) and 2.9 times after it (14^3, 12^3, 10^3
+// and 8^3): cheaper than the launches it saves while a level is a few rounds of
+// workgroups.
 //
 // Positions are counted in the local frame of a block's corner, which sits on
 // even nodes, so local and global colours agree.  A field in LDS covers the
@@ -842,9 +843,8 @@ hipError_t launch_tail(const T *const *a, const int *n, const T *scale, int leve
     return hipGetLastError();
 }
 
-// Tiles of 8^3 nodes where they divide the edge, else of 4^3 (every edge above
-// 16 is a multiple of 4).
-template <typename T>
+// Tiles of 8 x 4 x 4 nodes up to kTileSmall and of 8^3 above where 8 divides the
+// edge, else of 4^3 (every level's edge above 16 is a multiple of 4).
 bool tile_supported(int n)
 {
     return n > 16 && n % 4 == 0;
@@ -873,7 +873,7 @@ hipError_t post_shape(const T *a, const T *b, const T *u_in, const T *e, T *u_ou
 template <typename T>
 hipError_t launch_pre_tile(const T *a, const T *b, T *u, T *c, int n, T scale, T a_min, hipStream_t s)
 {
-    if (!tile_supported<T>(n) || !paired(a)) return hipErrorInvalidValue;
+    if (!tile_supported(n) || !paired(a)) return hipErrorInvalidValue;
     if (n % 8) return pre_shape<T, 4, 4, 4, 512>(a, b, u, c, n, scale, a_min, s);
     if (n <= kTileSmall) return pre_shape<T, 8, 4, 4, 576>(a, b, u, c, n, scale, a_min, s);
     return pre_shape<T, 8, 8, 8, 1024>(a, b, u, c, n, scale, a_min, s);
@@ -883,7 +883,7 @@ template <typename T>
 hipError_t launch_post_tile(const T *a, const T *b, const T *u_in, const T *e, T *u_out, int n, T scale, T a_min,
                             hipStream_t s)
 {
-    if (!tile_supported<T>(n) || u_in == u_out || !paired(a) || !paired(u_in)) return hipErrorInvalidValue;
+    if (!tile_supported(n) || u_in == u_out || !paired(a) || !paired(u_in)) return hipErrorInvalidValue;
     if (n % 8) return post_shape<T, 4, 4, 4, 512>(a, b, u_in, e, u_out, n, scale, a_min, s);
     if (n <= kTileSmall) return post_shape<T, 8, 4, 4, 576>(a, b, u_in, e, u_out, n, scale, a_min, s);
     return post_shape<T, 8, 8, 8, 1024>(a, b, u_in, e, u_out, n, scale, a_min, s);
@@ -892,7 +892,6 @@ hipError_t launch_post_tile(const T *a, const T *b, const T *u_in, const T *e, T
 #define RECON_INSTANTIATE(T)                                                                                  \
     template hipError_t launch_tail<T>(const T *const *, const int *, const T *, int, const T *, T *, T, int, int, int, \
                                         hipStream_t);                                          \
-    template bool tile_supported<T>(int);                                                                     \
     template hipError_t launch_pre_tile<T>(const T *, const T *, T *, T *, int, T, T, hipStream_t);           \
     template hipError_t launch_post_tile<T>(const T *, const T *, const T *, const T *, T *, int, T, T, hipStream_t);
 
